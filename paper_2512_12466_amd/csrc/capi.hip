@@ -73,13 +73,11 @@ const char* check_desc(const nrt_grid_desc* d) {
   return nullptr;
 }
 
-// Omega(l) = 4 pi / (12 4^l) (Eq. split_criterion); split iff s^2 > 1/(N_min Omega(l))
 void level_constants(nrt_ctx* c) {
-  for (int l = 0; l <= nrt::kMaxLevel; ++l) {
-    const double omega = (4.0 * M_PI) / (12.0 * std::ldexp(1.0, 2 * l));
-    c->sqrt_omega[l] = std::sqrt(omega);
-    c->r2split[l] = c->desc.n_min_ray > 0.0 ? 1.0 / (c->desc.n_min_ray * omega) : INFINITY;
-  }
+  for (int l = 0; l <= nrt::kMaxLevel; ++l)
+    c->s_split[l] = nrt::split_length(c->desc.n_min_ray, l);
+  c->line_mul[0] = nrt::line_multiplier(c->desc.n, nrt::kLog2LinesFp32);
+  c->line_mul[1] = nrt::line_multiplier(c->desc.n, nrt::kLog2LinesFp64);
 }
 
 nrt_status sync_read_accum(nrt_ctx* c) {
@@ -116,6 +114,8 @@ nrt_status upload_sources(nrt_ctx* c) {
 MarchArgs base_args(const nrt_ctx* c, double* gamma) {
   MarchArgs a = nrt::march_grid_args(c->desc, c->a64, gamma, c->acc);
   a.tau_stop = c->desc.spectrum != NRT_SPEC_MONO ? c->spec_tau_stop : c->desc.tau_max;
+  a.line_mul[0] = c->line_mul[0];
+  a.line_mul[1] = c->line_mul[1];
   a.src_pos = c->src_pos;
   a.src_l0 = c->src_l0;
   a.dirs = c->dirs;
@@ -162,8 +162,7 @@ nrt_status process_level(nrt_ctx* c, PassState& ps, int level, bool spawn, int64
     a.begin = b;
     a.end = e;
     a.in = c->queue[level];
-    a.r2split = c->r2split[level];
-    a.sqrt_omega = c->sqrt_omega[level];
+    a.s_stop = std::min(a.s_max, c->s_split[level]);
     a.claim_ctr = &c->acc->claim;
     unsigned long long* cnt = &c->acc->out_count[level + 1];
     if (!last) {
@@ -259,8 +258,7 @@ hipError_t enqueue_levels(nrt_ctx* c, hipStream_t st, double* gamma,
     a.count_src = level == 0 ? nullptr : &c->acc->out_count[level];
     a.in_cap = cap;
     a.in = c->queue[level];
-    a.r2split = c->r2split[level];
-    a.sqrt_omega = c->sqrt_omega[level];
+    a.s_stop = std::min(a.s_max, c->s_split[level]);
     a.claim_ctr = &c->acc->claim_lv[level];
     if (level < c->desc.l_max) {
       a.out = c->queue[level + 1];
@@ -545,6 +543,60 @@ const char* check_grid_desc(const nrt_grid_desc* d) { return check_desc(d); }
 
 void set_error(const char* msg) { set_init_error(msg); }
 
+// The slot of a line in a wavefront's deposit table is the top log2_lines bits
+// of (line * M mod 2^24).  A bundle of rays fills the lines of a few cells
+// around it, so M should send nearby lines (line +- 1 along x, n/8 along y,
+// n^2/8 along z) to different slots, which depends on n: of 64 multipliers,
+// the one with the least overlap of neighbours, weighted by a Gaussian of 4
+// cells.  An emulation of bundles on nine grids of 64^3 to 1024^3, 128 slots
+// folded at a quarter: a step of the wavefront probes past a first slot
+// 0.3 times with it, 0.8 times with the golden-ratio multiplier.
+uint32_t line_multiplier(int n, int log2_lines) {
+  constexpr int kReach = 5;
+  const uint32_t slot = 0x1000000u >> log2_lines;
+  double weight[2 * kReach * kReach + 1];
+  for (int r = 0; r <= 2 * kReach * kReach; ++r) weight[r] = std::exp(-r / 32.0);
+  double best = INFINITY;
+  uint32_t mul = 0, x = 0x9E3779B9u;
+  for (int q = 0; q < 64; ++q) {
+    x = x * 1664525u + 1013904223u;
+    const uint32_t m = (x >> 8) | 1u;
+    double score = 0.0;
+    for (int dz = 0; dz <= kReach; ++dz)
+      for (int dy = dz ? -kReach : 0; dy <= kReach; ++dy) {
+        const int64_t cells = int64_t(n) * dy + int64_t(n) * n * dz;
+        // rows that do not start on a line share one with both neighbours
+        const bool aligned = cells % 8 == 0;
+        for (int dx = dz || dy ? -1 : 1; dx <= (aligned ? 1 : 2); ++dx) {
+          const uint32_t p = (uint32_t(cells >> 3) + uint32_t(dx)) * m & 0xffffffu;
+          const uint32_t gap = p >= 0x800000u ? 0x1000000u - p : p;
+          const int cx = 8 * dx - (aligned ? 0 : 4);
+          if (gap < slot)
+            score += double(slot - gap) * weight[dy * dy + dz * dz] * (cx == 0 ? 1.0 : std::exp(-cx * cx / 32.0));
+        }
+      }
+    if (score < best) {
+      best = score;
+      mul = m;
+    }
+  }
+  return mul;
+}
+
+// Omega(l) = 4 pi / (12 4^l) (Eq. split_criterion), Omega_c = 1 / s^2: a ray
+// splits iff s*s > 1 / (N_min Omega(l)).  The rounded square is monotone in
+// s, so the test is a comparison with the smallest s that passes it, found
+// here a few steps from the square root.
+double split_length(double n_min_ray, int level) {
+  if (!(n_min_ray > 0.0)) return INFINITY;
+  const double omega = (4.0 * M_PI) / (12.0 * std::ldexp(1.0, 2 * level));
+  const double r2 = 1.0 / (n_min_ray * omega);
+  double s = std::sqrt(r2);
+  while (s > 0.0 && s * s > r2) s = std::nextafter(s, 0.0);
+  while (!(s * s > r2) && s < INFINITY) s = std::nextafter(s, INFINITY);
+  return s;
+}
+
 MarchArgs march_grid_args(const nrt_grid_desc& d, const double* a64,
                           double* gamma, Accum* acc) {
   MarchArgs a;
@@ -558,6 +610,7 @@ MarchArgs march_grid_args(const nrt_grid_desc& d, const double* a64,
   a.tau_max = d.tau_max;
   a.s_max = d.periodic ? std::sqrt(3.0) * double(d.n) : INFINITY;
   a.h3 = d.h_cm * d.h_cm * d.h_cm;
+  a.inv_n = 1.0 / double(d.n);
   a.inv_h3 = 1.0 / a.h3;
   a.tau_stop = d.tau_max;
   a.kf = float(d.sigma0 * d.h_cm);
@@ -569,7 +622,6 @@ MarchArgs march_grid_args(const nrt_grid_desc& d, const double* a64,
     a.sqrt_omega_tab[l] = std::sqrt(omega);
   }
   a.acc = acc;
-  a.lds_keys_fit = ((int64_t(d.n) * d.n * d.n) >> 3 < (int64_t(1) << 32) - 1) ? 1 : 0;
   return a;
 }
 
@@ -891,6 +943,7 @@ nrt_status nrt_trace_rays_debug(nrt_ctx* c, int64_t k, const double* origin, con
   if (k > 0) {
     MarchArgs a = base_args(c, gamma_out);
     a.level = -1;
+    a.s_stop = a.s_max;
     a.begin = 0;
     a.end = k;
     a.inj_origin = d_org;

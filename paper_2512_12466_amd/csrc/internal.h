@@ -16,6 +16,9 @@ namespace nrt {
 constexpr int kMaxLevel = NRT_MAX_LEVEL;
 constexpr int kBlock = 256;  // threads per block of the march kernels (4 waves)
 
+// Line slots of a wavefront's deposit table (trace.hip), by the type of its sums.
+constexpr int kLog2LinesFp32 = 8, kLog2LinesFp64 = 7;
+
 // One ray in a level queue (structure of arrays, 24 bytes per ray).  The
 // HEALPix level is the queue's, the rate follows from the source and level,
 // and the direction from (level, pix).  w is the optical depth tau at the
@@ -82,13 +85,14 @@ struct MarchArgs {
   int32_t n, periodic, corr, l_max;
   int32_t level;     // HEALPix level of every input ray (-1: injected rays)
   int32_t spawn;     // 1: input ray r is (src_begin + r/12, pix r%12, s 0, w 0/1)
-  int32_t lds_keys_fit;  // 1: line indices (cell >> 3) fit 32 bits (Gamma staged in LDS)
   int32_t refill_min;    // idle lanes that trigger a refill of a wavefront
   int64_t claim;         // rays a wavefront claims at a time
+  uint32_t line_mul[2];  // slot hash multipliers of the deposit table, FP32 and FP64 sums
   double h_cm, sigma0, tau_max, s_max, h3;
+  double inv_n;      // 1 / n
   double inv_h3;     // 1 / h^3 (the mixed path's FP32 deposit scale)
-  double r2split;    // split iff s*s > r2split (this level)
-  double sqrt_omega; // sqrt of the pixel solid angle (this level)
+  double s_stop;     // smallest s at which a ray of this launch stops: s_max, or the
+                     // smallest double with s*s > r2split of its level
   double tau_stop;   // the ray stops once tau >= tau_stop: tau_max for a
                      // monochromatic source; for a spectrum the threshold
                      // optical depth at which Phi(tau) reaches tau_max
@@ -147,6 +151,13 @@ Layout plan_layout(const nrt_grid_desc& d, int64_t max_sources, int64_t capacity
 MarchArgs march_grid_args(const nrt_grid_desc& d, const double* a64,
                           double* gamma, Accum* acc);
 
+// multiplier of the deposit table's slot hash for an n^3 grid and 2^log2_lines slots
+uint32_t line_multiplier(int n, int log2_lines);
+
+// smallest path length at which a ray of a level splits (Eq. split_criterion):
+// the smallest double s with s*s > 1 / (N_min Omega(level))
+double split_length(double n_min_ray, int level);
+
 // the reason a grid descriptor is invalid, or NULL (capi.hip)
 const char* check_grid_desc(const nrt_grid_desc* d);
 // set the message nrt_last_error(NULL) returns (fixed storage, no allocation)
@@ -201,8 +212,8 @@ struct nrt_ctx {
   // pinned host staging for small readbacks
   nrt::Accum* h_acc;
   // per-level constants (host-computed, FP64)
-  double r2split[nrt::kMaxLevel + 1];
-  double sqrt_omega[nrt::kMaxLevel + 1];
+  double s_split[nrt::kMaxLevel + 1];
+  uint32_t line_mul[2];  // see MarchArgs
   // timing of the last pass
   std::vector<hipEvent_t> ev;
   int launches;

@@ -157,10 +157,20 @@ nrt_status nrt_trace_step_noalloc(const nrt_grid_desc* desc, const double* n_H,
   // the device-driven pass: one launch per HEALPix level, each reading its
   // ray count from the count the previous level wrote
   const nrt_tuning t = {0, 0, 0, 0};
+  // the hash multipliers of the last grid size a thread called with
+  thread_local int mul_n = 0;
+  thread_local uint32_t mul[2];
+  if (mul_n != desc->n) {
+    mul[0] = nrt::line_multiplier(desc->n, nrt::kLog2LinesFp32);
+    mul[1] = nrt::line_multiplier(desc->n, nrt::kLog2LinesFp64);
+    mul_n = desc->n;
+  }
   for (int level = 0; level <= desc->l_max && m > 0; ++level) {
     nrt::MarchArgs a = nrt::march_grid_args(*desc, a64, gamma_out, acc);
     a.src_pos = src_pos;
     a.src_l0 = src_l0;
+    a.line_mul[0] = mul[0];
+    a.line_mul[1] = mul[1];
     a.level = level;
     a.spawn = level == 0 ? 1 : 0;
     a.begin = 0;
@@ -168,9 +178,7 @@ nrt_status nrt_trace_step_noalloc(const nrt_grid_desc* desc, const double* n_H,
     a.count_src = level == 0 ? nullptr : &acc->out_count[level];
     a.in_cap = ray_capacity;
     a.in = q[level];
-    const double omega = (4.0 * M_PI) / (12.0 * std::ldexp(1.0, 2 * level));
-    a.r2split = desc->n_min_ray > 0.0 ? 1.0 / (desc->n_min_ray * omega) : INFINITY;
-    a.sqrt_omega = std::sqrt(omega);
+    a.s_stop = std::fmin(a.s_max, nrt::split_length(desc->n_min_ray, level));
     a.claim_ctr = &acc->claim_lv[level];
     if (level < desc->l_max) {
       a.out = q[level + 1];

@@ -31,17 +31,21 @@ namespace nrt {
 
 namespace {
 
+// wrapped coordinate; cells lie within a few box lengths of the box, so
+// whole-box steps replace the integer division (which the compiler would make
+// of the loops again, hence the empty asm)
 __device__ __forceinline__ int wrap_cell(int i, int n) {
-  // start cells lie within a few box lengths of the box: conditional steps
-  // instead of an integer division
-  if (i >= -2 * n && i < 3 * n) {
-    int r = i < 0 ? i + n : i;
-    r = r < 0 ? r + n : r;
-    r = r >= n ? r - n : r;
-    return r >= n ? r - n : r;
+#pragma unroll 1
+  while (i < 0) {
+    i += n;
+    asm volatile("" : "+v"(i));
   }
-  const int r = i % n;
-  return r < 0 ? r + n : r;
+#pragma unroll 1
+  while (i >= n) {
+    i -= n;
+    asm volatile("" : "+v"(i));
+  }
+  return i;
 }
 
 // Flat index of the wrapped cell (w0, w1, w2), x fastest.  n <= 4096, so the
@@ -50,22 +54,6 @@ __device__ __forceinline__ int wrap_cell(int i, int n) {
 __device__ __forceinline__ int64_t cell_index(int w0, int w1, int w2, int n) {
   const uint32_t plane = uint32_t(w1) + __umul24(uint32_t(n), uint32_t(w2));
   return int64_t(uint64_t(uint32_t(w0)) + uint64_t(uint32_t(n)) * uint64_t(plane));
-}
-
-// one step of a wrapped coordinate
-__device__ __forceinline__ int wrap_step(int w, int step, int n) {
-  w += step;
-  if (w >= n) w -= n;
-  if (w < 0) w += n;
-  return w;
-}
-
-// parametric distance from the source to the next plane of one axis: one
-// division whatever the sign (lanes of a wavefront differ in it), +inf for a
-// zero component
-__device__ __forceinline__ double plane_t(double o, double d, int i) {
-  const double t = (double(d > 0.0 ? i + 1 : i) - o) / d;
-  return d != 0.0 ? t : __builtin_inf();
 }
 
 // start cell of a ray at q = o + s d: floor(q), except that an exact integer
@@ -103,20 +91,28 @@ __device__ __forceinline__ ArgsK& fresh_args() {
 
 struct LaneAcc {
   double absorbed = 0.0, escaped = 0.0, truncated = 0.0;
-  unsigned long long segments = 0;
+  uint32_t segments = 0;  // of one lane in one launch
 };
 
 // Per-wavefront Gamma accumulator in LDS.  A wavefront marches rays claimed
 // in runs of consecutive queue entries; nested HEALPix order is a Z-order
 // curve and children are queued next to each other, so such a run is a
 // bundle of neighbouring pixels of one source and level, and by the split
-// rule it crosses each cell several times.  Deposits are summed in an
-// open-addressing hash table whose slots are 64-byte lines of Gamma (kLine
-// consecutive cells along x), and folded into Gamma when a quarter of the
-// slots are taken: the device performs FP64 atomics per 64-byte line
-// request, so the flush, in which lanes 8j..8j+7 of an instruction cover the
-// cells of one line, costs one request per line instead of one per cell.  A deposit that
-// finds no slot within kProbe probes goes straight to Gamma.
+// rule it crosses each cell several times.  Deposits are summed in a hash
+// table whose slots are 64-byte lines of Gamma (kLine consecutive cells along
+// x), and folded into Gamma when enough of the slots are taken: the device
+// performs FP64 atomics per 64-byte line request, so the flush, in which
+// lanes 8j..8j+7 of an instruction cover the cells of one line, costs one
+// request per line instead of one per cell.
+//
+// What bounds it is the LDS pipe.  Measured on MI355X with 16 wavefronts a
+// CU, in cycles per wavefront instruction: a 4-byte read 7.8 whatever the
+// addresses; a compare-and-swap 10.6, but 35 / 64 when 4 / 8 lanes share an
+// address; an FP64 add 13.6, 48 / 96; an FP32 add 198, 244 / 253 (it takes the
+// lanes one by one).  So a deposit reads its slot's key and swaps only where
+// its line is new, instead of a swap by every lane, and deposits are summed
+// in FP64 (see march_kernel for the exception).  A deposit that finds no slot
+// within kProbe probes goes straight to Gamma.
 constexpr int kWaves = kBlock / 64;
 constexpr int kLine = 8;
 constexpr int kProbe = 16;
@@ -124,75 +120,95 @@ constexpr uint32_t kEmpty = 0xffffffffu;
 
 template <typename V>
 struct LineTable {
-  // line slots per wavefront: 36 KiB (FP32 sums) or 34 KiB (FP64) per block
-  static constexpr int kLog2Lines = sizeof(V) == 4 ? 8 : 7;
+  // line slots per wavefront: 37 KiB (FP32 sums) or 34.5 KiB (FP64) per block
+  static constexpr int kLog2Lines = sizeof(V) == 4 ? kLog2LinesFp32 : kLog2LinesFp64;
   static constexpr int kLines = 1 << kLog2Lines;
-  // fold at a quarter full: probe collisions cost more than the folds saved
-  // (measured on the 1024^3 field: 1/4 84.3, 1/2 80.3, 3/4 68.8 G segments/s)
   static constexpr int kFlushAt = kLines / 4;
-  static constexpr size_t kWaveBytes = kLines * (sizeof(uint32_t) + kLine * sizeof(V));
+  static constexpr size_t kWaveBytes =
+      kLines * (sizeof(uint32_t) + sizeof(uint8_t) + kLine * sizeof(V));
 
-  uint32_t* key;  // [kLines] line index (cell >> 3) or kEmpty
+  uint32_t* key;  // [kLines] line index (cell >> 3, below 2^32 - 1 on any grid that fits the
+                  // device's memory) or kEmpty
   V* val;         // [kLines * kLine] partial sums of the line's cells
-  bool on;        // false when line indices do not fit 32 bits below kEmpty
+  uint8_t* list;  // [kLines] slots in use, compacted by a flush
+  uint32_t mul;   // multiplier of the slot hash (line_multiplier)
 
-  // First probe for the line of cell c, issued ahead of the arithmetic that
-  // precedes the deposit, so that the compare-and-swap is in flight while it
-  // runs; `deposit` consumes its result.
-  struct Claim {
+  // First slot of the line of cell c and the key it holds, read ahead of the
+  // arithmetic that precedes the deposit.
+  struct Look {
     uint32_t k, h, old;
   };
-  __device__ __forceinline__ Claim claim(int64_t c) const {
-    Claim cl{uint32_t(c >> 3), 0u, 0u};
-    if (on) {
-      cl.h = (cl.k * 2654435761u) >> (32 - kLog2Lines);
-      cl.old = atomicCAS(&key[cl.h], kEmpty, cl.k);
-    }
-    return cl;
+  template <typename Idx>
+  __device__ __forceinline__ Look look(Idx c) const {
+    Look l;
+    l.k = uint32_t(c >> 3);
+    uint32_t product;  // full rate; the compiler would take the 32-bit multiply
+    asm("v_mul_u32_u24 %0, %1, %2" : "=v"(product) : "s"(mul), "v"(l.k));
+    l.h = (product >> (24 - kLog2Lines)) & uint32_t(kLines - 1);
+    l.old = key[l.h];
+    return l;
   }
-  // whether the claim took a new slot (it stays taken even if no value follows)
-  __device__ __forceinline__ static bool took(const Claim& cl) { return cl.old == kEmpty; }
 
-  // add v for cell c to the slot of its claim, probing further if the first
-  // slot belongs to another line
-  __device__ __forceinline__ int deposit(const Claim& cl, int64_t c, V v) const {
-    if (on) {
-      const uint32_t sub = uint32_t(c) & uint32_t(kLine - 1);
-      if (cl.old == kEmpty || cl.old == cl.k) {
-        atomicAdd(&val[cl.h * kLine + sub], v);
-        return 0;
+  // Take the slot of a line that it did not hold when it was read (lanes with
+  // claim); counts a new line in `inserted`.  After it, l.old == l.k tells
+  // that the slot is the line's.
+  __device__ __forceinline__ void claim(Look& l, bool claim, int& inserted) const {
+    if (claim && l.old != l.k) {
+      l.old = atomicCAS(&key[l.h], kEmpty, l.k);
+      if (l.old == kEmpty) {
+        l.old = l.k;
+        ++inserted;
       }
-      uint32_t h = cl.h;
+    }
+  }
+
+  // add v for cell c (lanes with want) to the line's slot, probing further
+  // (lanes with claim) if its first slot belongs to another line
+  template <typename Idx>
+  __device__ __forceinline__ void deposit(Look& l, Idx c, V v, bool claim, bool want,
+                                          int& inserted) const {
+    const uint32_t sub = uint32_t(c) & uint32_t(kLine - 1);
+    if (claim && l.old != l.k) {
 #pragma unroll 1
       for (int probe = 1; probe < kProbe; ++probe) {
-        h = (h + 1) & uint32_t(kLines - 1);
-        const uint32_t old = atomicCAS(&key[h], kEmpty, cl.k);
-        if (old == kEmpty || old == cl.k) {
-          atomicAdd(&val[h * kLine + sub], v);
-          return old == kEmpty ? 1 : 0;
-        }
+        l.h = (l.h + 1) & uint32_t(kLines - 1);
+        l.old = atomicCAS(&key[l.h], kEmpty, l.k);
+        if (l.old == kEmpty || l.old == l.k) break;
       }
+      if (l.old == kEmpty) {
+        l.old = l.k;
+        ++inserted;
+      }
+      if (want && l.old != l.k) atomicAdd(fresh_args().gamma + c, double(v));
     }
-    atomicAdd(fresh_args().gamma + c, double(v));
-    return 0;
+    if (want && l.old == l.k) atomicAdd(&val[l.h * kLine + sub], v);
   }
 
   // whole wavefront: fold the table into Gamma and clear it (LDS operations
-  // of one wavefront complete in program order).  Cells of a line that got
-  // no deposit hold zero and are skipped, so no address past the grid is
-  // formed.
+  // of one wavefront complete in program order).  The slots in use are listed
+  // first, so that the fold takes 8 lines an iteration however few they are.
+  // Cells of a line that got no deposit hold zero and are skipped, so no
+  // address past the grid is formed.
   __device__ __forceinline__ void flush(int lane) const {
     double* gamma = fresh_args().gamma;
     __builtin_amdgcn_wave_barrier();
+    int used = 0;
+#pragma unroll
+    for (int q = 0; q < kLines; q += 64) {
+      const bool full = key[q + lane] != kEmpty;
+      const uint64_t m = __ballot(full);
+      if (full) list[used + int(lanes_below(m))] = uint8_t(q + lane);
+      used += __popcll(m);
+    }
+    __builtin_amdgcn_wave_barrier();
     const int sub = lane & (kLine - 1);
-    for (int q = lane / kLine; q < kLines; q += 64 / kLine) {
-      const uint32_t k = key[q];
-      if (k != kEmpty) {
-        const V v = val[q * kLine + sub];
-        if (v != V(0)) {
-          atomicAdd(gamma + ((int64_t(k) << 3) + sub), double(v));
-          val[q * kLine + sub] = V(0);
-        }
+    for (int q = lane / kLine; q < used; q += 64 / kLine) {
+      const uint32_t slot = list[q];
+      const uint32_t k = key[slot];
+      const V v = val[slot * kLine + sub];
+      if (v != V(0)) {
+        atomicAdd(gamma + ((int64_t(k) << 3) + sub), double(v));
+        val[slot * kLine + sub] = V(0);
       }
     }
     __builtin_amdgcn_wave_barrier();
@@ -210,22 +226,49 @@ constexpr int kGoOn = 0, kEscaped = 1, kTruncated = 2, kSplit = 3;
 // fits 5 bits
 constexpr int kCellsPerIteration = 8;
 
-// State of the ray a lane is marching.  Unwrapped cell coordinates (i) keep
-// the plane crossings exact across periodic wraps; wrapped ones (w) address
-// memory.
+// State of the ray a lane is marching.  The axes along which the ray points
+// down are mirrored (origin and planes negated, exactly), so that every ray
+// runs upwards on every axis: the next plane of an axis is the cell's upper
+// one, a step adds 1 to it, and "ahead" and "behind" replace upper and lower.
+// Rounding is symmetric, so every value equals the unmirrored one up to its
+// sign.  Planes are unwrapped, which keeps crossings exact across periodic
+// wraps; the wrapped flat cell index and signed strides address memory.
+template <typename Idx>
 struct RayState {
-  double o0, o1, o2, d0, d1, d2;
-  double t0, t1, t2;
+  double o0, o1, o2, d0, d1, d2;  // mirrored origin, |direction|
+  double r0, r1, r2;              // RN(1 / d); kFarRate for a zero component
+  double p0, p1, p2;              // next plane of each axis (an integer)
   double s, L;
   double tau;       // optical depth at the threshold (FP64, both paths)
   double P;         // photons carried (FP64 path)
   double T;         // mixed path: transmitted fraction
   float s_rate;     // mixed path: L / h^3 in FP32
   double a64;       // absorber of the current cell, loaded ahead
-  int i0, i1, i2, w0, w1, w2;
-  int level;
+  double so;        // sqrt of the pixel solid angle
+  // a crossing at s <= s_in leaves a cell off the box's boundary layer for
+  // another one: neither it nor a face neighbour's index wraps or leaves
+  double s_in;
+  Idx c;            // wrapped flat index of the current cell
+  int st0, st1, st2;  // signed strides: +-1, +-n, +-n^2
   uint32_t src, pix;
 };
+
+// reciprocal of a zero component: crossings of its planes come last
+constexpr double kFarRate = 1e290;
+
+// (p - o) / d, correctly rounded, from r = RN(1 / d): q1 is within 2^-104 of
+// the quotient before its rounding, so faithful, and Markstein's theorem (a
+// faithful quotient corrected once by its exact remainder times RN(1 / d)
+// rounds correctly) makes q2 the IEEE quotient.  Six full-rate operations
+// where the division takes fourteen, one of them quarter rate; cheap enough
+// to form all three axes' crossings every step instead of selecting and
+// storing back the one that moved (18 operations against 28).
+__device__ __forceinline__ double crossing(double p, double o, double d, double r) {
+  const double a = p - o;
+  const double q0 = a * r;
+  const double q1 = fma(fma(-q0, d, a), r, q0);
+  return fma(fma(-q1, d, a), r, q1);
+}
 
 // ---- polychromatic sources: Phi(tau) = -ln F(tau) from the table ----
 struct SpecPos {
@@ -363,47 +406,86 @@ __device__ __forceinline__ Entry load_entry(Args& A, int64_t r) {
   return e;
 }
 
+// The box plane ahead of the cell below plane p, on one (mirrored) axis: box
+// planes are the multiples of n, and (p - 1/2) / n is at least 1/(2n) from an
+// integer, so the rounded reciprocal of n decides its floor rightly.
+__device__ __forceinline__ double box_plane(double p, double n, double inv_n) {
+  return (floor((p - 0.5) * inv_n) + 1.0) * n;
+}
+
+// Path length up to which a ray's crossings stay off the boundary layer, from
+// its distances f to the box planes h ahead (in cells, 0 in the last cell):
+// -1 in the layer; else 1e-12 short of its entry, so rounding cannot put it
+// late.
+template <typename Idx>
+__device__ __forceinline__ double inner_length(const RayState<Idx>& R, double f0, double f1,
+                                               double f2, double h0, double h1, double h2,
+                                               double n) {
+  const double e0 = ((h0 - 1.0) - R.o0) * R.r0;
+  const double e1 = ((h1 - 1.0) - R.o1) * R.r1;
+  const double e2 = ((h2 - 1.0) - R.o2) * R.r2;
+  const double lo = fmin(fmin(f0, f1), f2), hi = fmax(fmax(f0, f1), f2);
+  return lo >= 1.0 && hi <= n - 2.0 ? fmin(fmin(e0, e1), e2) * (1.0 - 1e-12) : -1.0;
+}
+
 // Start the ray of entry e: direction, start cell and first absorber.
 // Returns kEscaped if it starts outside an open box, else kGoOn.
-template <bool MIXED, bool PERIODIC, bool POLY, typename Args>
-__device__ int ray_init(RayState& R, Args& A, const Entry& e) {
+template <bool MIXED, bool PERIODIC, bool POLY, typename Idx, typename Args>
+__device__ __forceinline__ int ray_init(RayState<Idx>& R, Args& A, const Entry& e) {
   double w = e.w;
+  int level;
+  double o0, o1, o2, d0, d1, d2;
   if (A.level < 0) {  // injected rays: never split
     const int64_t r = e.src;
-    R.o0 = A.inj_origin[3 * r];
-    R.o1 = A.inj_origin[3 * r + 1];
-    R.o2 = A.inj_origin[3 * r + 2];
-    R.d0 = A.inj_dir[3 * r];
-    R.d1 = A.inj_dir[3 * r + 1];
-    R.d2 = A.inj_dir[3 * r + 2];
+    o0 = A.inj_origin[3 * r];
+    o1 = A.inj_origin[3 * r + 1];
+    o2 = A.inj_origin[3 * r + 2];
+    d0 = A.inj_dir[3 * r];
+    d1 = A.inj_dir[3 * r + 1];
+    d2 = A.inj_dir[3 * r + 2];
     R.L = A.inj_L[r];
-    R.level = A.inj_level[r];
+    level = A.inj_level[r];
     R.s = 0.0;
     R.src = R.pix = 0;
   } else {
     R.src = e.src;
     R.pix = e.pix;
     R.s = e.s;
-    R.level = A.level;
-    R.o0 = A.src_pos[3 * int64_t(R.src)];
-    R.o1 = A.src_pos[3 * int64_t(R.src) + 1];
-    R.o2 = A.src_pos[3 * int64_t(R.src) + 2];
-    R.L = ldexp(A.src_l0[R.src], -2 * R.level);
-    if (R.level <= A.dir_max_level) {  // the table holds this device function's values
-      const double* d = A.dirs + 3 * (dir_table_offset(R.level) + int64_t(R.pix));
-      R.d0 = d[0];
-      R.d1 = d[1];
-      R.d2 = d[2];
+    level = A.level;
+    o0 = A.src_pos[3 * int64_t(R.src)];
+    o1 = A.src_pos[3 * int64_t(R.src) + 1];
+    o2 = A.src_pos[3 * int64_t(R.src) + 2];
+    R.L = ldexp(A.src_l0[R.src], -2 * level);
+    if (level <= A.dir_max_level) {  // the table holds this device function's values
+      const double* d = A.dirs + 3 * (dir_table_offset(level) + int64_t(R.pix));
+      d0 = d[0];
+      d1 = d[1];
+      d2 = d[2];
     } else {
-      healpix_dir(R.level, R.pix, R.d0, R.d1, R.d2);
+      healpix_dir(level, R.pix, d0, d1, d2);
     }
   }
-  R.i0 = start_cell(R.o0, R.s, R.d0);
-  R.i1 = start_cell(R.o1, R.s, R.d1);
-  R.i2 = start_cell(R.o2, R.s, R.d2);
-  R.t0 = plane_t(R.o0, R.d0, R.i0);
-  R.t1 = plane_t(R.o1, R.d1, R.i1);
-  R.t2 = plane_t(R.o2, R.d2, R.i2);
+  // sqrt of the pixel solid angle: sqrt(Omega(0)) 2^-level, exactly
+  R.so = ldexp(A.sqrt_omega_tab[0], -level);
+  const int n = A.n;
+  const int i0 = start_cell(o0, R.s, d0);
+  const int i1 = start_cell(o1, R.s, d1);
+  const int i2 = start_cell(o2, R.s, d2);
+  // components that no crossing in any box can see count as zero (injected
+  // rays only; the smallest nonzero component of a pixel centre is ~1e-5)
+  auto axis = [](double o, double d, int i, int stride, double& ro, double& rd, double& rr,
+                 double& rp, int& rst) {
+    const bool down = d < 0.0;
+    const double m = fabs(d);
+    ro = down ? -o : o;
+    rd = m > 1e-280 ? m : 0.0;
+    rr = m > 1e-280 ? 1.0 / m : kFarRate;
+    rp = double(down ? -i : i + 1);
+    rst = down ? -stride : stride;
+  };
+  axis(o0, d0, i0, 1, R.o0, R.d0, R.r0, R.p0, R.st0);
+  axis(o1, d1, i1, n, R.o1, R.d1, R.r1, R.p1, R.st1);
+  axis(o2, d2, i2, n * n, R.o2, R.d2, R.r2, R.p2, R.st2);
   R.tau = w;
   // transmitted share of the ray's photons: e^{-tau}, or e^{-Phi(tau)} for a
   // spectrum (exactly 1 at a source)
@@ -414,13 +496,15 @@ __device__ int ray_init(RayState& R, Args& A, const Entry& e) {
   } else {
     R.P = R.L * T;
   }
-  const int n = A.n;
-  const bool out = R.i0 < 0 || R.i0 >= n || R.i1 < 0 || R.i1 >= n || R.i2 < 0 || R.i2 >= n;
+  const bool out = i0 < 0 || i0 >= n || i1 < 0 || i1 >= n || i2 < 0 || i2 >= n;
   if (!PERIODIC && out) return kEscaped;
-  R.w0 = PERIODIC ? wrap_cell(R.i0, n) : R.i0;
-  R.w1 = PERIODIC ? wrap_cell(R.i1, n) : R.i1;
-  R.w2 = PERIODIC ? wrap_cell(R.i2, n) : R.i2;
-  R.a64 = A.a64[cell_index(R.w0, R.w1, R.w2, n)];
+  R.c = Idx(PERIODIC ? cell_index(wrap_cell(i0, n), wrap_cell(i1, n), wrap_cell(i2, n), n)
+                     : cell_index(i0, i1, i2, n));
+  R.a64 = A.a64[R.c];
+  const double nd = double(n);
+  const double h0 = box_plane(R.p0, nd, A.inv_n), h1 = box_plane(R.p1, nd, A.inv_n),
+               h2 = box_plane(R.p2, nd, A.inv_n);
+  R.s_in = inner_length(R, h0 - R.p0, h1 - R.p1, h2 - R.p2, h0, h1, h2, nd);
   return kGoOn;
 }
 
@@ -432,14 +516,25 @@ __device__ int ray_init(RayState& R, Args& A, const Entry& e) {
 // empty asm statement makes each value the output of an instruction, which
 // cannot be reloaded, so it stays in a register.
 struct StepConst {
-  double s_max, tau_stop, sigma0;
+  double s_stop, tau_stop, sigma0;
   __device__ explicit StepConst(const MarchArgs& A)
-      : s_max(A.s_max), tau_stop(A.tau_stop), sigma0(A.sigma0) {
-    asm volatile("" : "+s"(s_max));
+      : s_stop(A.s_stop), tau_stop(A.tau_stop), sigma0(A.sigma0) {
+    asm volatile("" : "+s"(s_stop));
     asm volatile("" : "+s"(tau_stop));
     asm volatile("" : "+s"(sigma0));
   }
 };
+
+// Why a ray whose path length or optical depth reached the launch's bound
+// stops, in the method's order: the end of a periodic ray, the optical-depth
+// cap (for a spectrum: the threshold optical depth at which the share of
+// photons left falls to e^{-tau_max}), then the split.
+template <bool PERIODIC, typename Args, typename Idx>
+__device__ __forceinline__ int stop_code(const Args& A, const RayState<Idx>& R) {
+  if (PERIODIC && R.s >= A.s_max) return kEscaped;
+  if (R.tau >= A.tau_stop) return kTruncated;
+  return A.level >= A.l_max ? kTruncated : kSplit;
+}
 
 // Stop tests at the current cell boundary, then one cell segment: optical
 // depth, Eq. lut_eqn deposit with the overlap correction, advance.  The
@@ -448,92 +543,102 @@ struct StepConst {
 // the cell's absorber was loaded at the end of the previous step; the
 // neighbour's is requested by every lane (its own cell's when it needs no
 // neighbour), so that the wait for the cell's word leaves that request in
-// flight; the table claims are issued after the attenuation and before the
-// advance, whose arithmetic covers them and the neighbour's load, and the
-// deposits come last.
-template <bool MIXED, int CORR, bool PERIODIC, bool POLY, typename V>
-__device__ int ray_step(RayState& R, const MarchArgs& A, const LineTable<V>& tab, LaneAcc& acc,
-                        int& inserted, const StepConst& K) {
-  const int n = A.n;
-  constexpr bool open_box = !PERIODIC;
-  if (PERIODIC && R.s >= K.s_max) return kEscaped;
-  // the optical-depth cap (for a spectrum: the threshold optical depth at
-  // which the share of photons left falls to e^{-tau_max})
-  if (R.tau >= K.tau_stop) return kTruncated;
-  // split radius^2 of the launch's level (injected rays never split)
-  const double r2s = A.level < 0 ? __builtin_inf() : A.r2split;
-  if (R.s * R.s > r2s) return R.level >= A.l_max ? kTruncated : kSplit;
+// flight; the table's keys are read before the attenuation, new lines are
+// claimed after it and before the advance, whose arithmetic covers the claims
+// and the neighbour's load, and the deposits come last.
+template <bool MIXED, int CORR, bool PERIODIC, bool POLY, typename V, typename Idx>
+__device__ __forceinline__ int ray_step(RayState<Idx>& R, const MarchArgs& A,
+                                        const LineTable<V>& tab, LaneAcc& acc, int& inserted,
+                                        const StepConst& K) {
+  constexpr bool neighbours = CORR == NRT_CORR_CONSERVATIVE || CORR == NRT_CORR_NAIVE;
+  if (R.s >= K.s_stop || R.tau >= K.tau_stop) return stop_code<PERIODIC>(fresh_args(), R);
+  const Idx c = R.c;
+  auto l1 = tab.look(c);
   // next crossing: lowest axis wins exact ties
-  int ax = 0;
-  double tn = R.t0;
-  if (R.t1 < tn) {
-    ax = 1;
-    tn = R.t1;
-  }
-  if (R.t2 < tn) {
-    ax = 2;
-    tn = R.t2;
-  }
-  double ds = tn - R.s;
-  if (ds < 0.0) ds = 0.0;
-  const int64_t c = cell_index(R.w0, R.w1, R.w2, n);
+  const double t0 = crossing(R.p0, R.o0, R.d0, R.r0);
+  const double t1 = crossing(R.p1, R.o1, R.d1, R.r1);
+  const double t2 = crossing(R.p2, R.o2, R.d2, R.r2);
+  const bool x1 = t1 < t0;
+  const double t01 = fmin(t0, t1);
+  const bool x2 = t2 < t01;
+  const double tn = fmin(t01, t2);
+  const double ds = fmax(tn - R.s, 0.0);
+  const int st0 = R.st0, st1 = R.st1, st2 = R.st2;
+  const int st_x = x2 ? st2 : (x1 ? st1 : st0);
+  Idx cn = c + Idx(st_x);
 
   // ---- overlap geometry (Eqs. correction .. new_secondary): nearest face
   // of the segment midpoint, and the neighbour across it ----
   bool near = false;
   double dedge = 0.0, lpix = 1.0;
   bool neighbour = false;  // the neighbour's absorber is needed
-  int64_t c2 = 0;
+  Idx c2 = c;
   double raw2_64 = 0.0;
-  float raw2_32 = 0.0f;
+  bool behind = false, f1 = false, f2 = false;  // the face: side and axis
   if constexpr (CORR != NRT_CORR_NONE) {
     const double rm = 0.5 * (R.s + tn);
-    // sqrt of the pixel solid angle: sqrt(Omega(0)) 2^-level, exactly
-    lpix = rm * ldexp(A.sqrt_omega_tab[0], -R.level);
-    // per axis: distance to the nearer face and its side (-1 lower, +1
-    // upper; an exact tie goes the way the ray points); the first axis wins
-    // ties between axes.  Selects only, no branches.
-    const double m0 = R.o0 + rm * R.d0;
-    const double dm0 = m0 - double(R.i0), dp0 = double(R.i0 + 1) - m0;
-    const double m1 = R.o1 + rm * R.d1;
-    const double dm1 = m1 - double(R.i1), dp1 = double(R.i1 + 1) - m1;
-    const double m2 = R.o2 + rm * R.d2;
-    const double dm2 = m2 - double(R.i2), dp2 = double(R.i2 + 1) - m2;
-    // both comparisons up front, so that the side is two selects
-    const bool lt0 = dm0 < dp0, gt0 = dp0 < dm0;
-    const bool lt1 = dm1 < dp1, gt1 = dp1 < dm1;
-    const bool lt2 = dm2 < dp2, gt2 = dp2 < dm2;
-    const int s0 = lt0 ? -1 : (gt0 ? 1 : (R.d0 < 0.0 ? -1 : 1));
-    const int s1 = lt1 ? -1 : (gt1 ? 1 : (R.d1 < 0.0 ? -1 : 1));
-    const int s2 = lt2 ? -1 : (gt2 ? 1 : (R.d2 < 0.0 ? -1 : 1));
-    const double da0 = lt0 ? dm0 : dp0;
-    const double da1 = lt1 ? dm1 : dp1;
-    const double da2 = lt2 ? dm2 : dp2;
-    const bool b1 = da1 < da0;
-    const double d01 = b1 ? da1 : da0;
-    const bool b2 = da2 < d01;
-    dedge = b2 ? da2 : d01;
-    const int fax = b2 ? 2 : (b1 ? 1 : 0);
-    const int fdir = b2 ? s2 : (b1 ? s1 : s0);
+    lpix = rm * R.so;
+    // per axis: distance to the nearer face; an exact tie goes the way the
+    // ray points (ahead); the first axis wins ties between axes
+    const double m0 = R.o0 + rm * R.d0, m1 = R.o1 + rm * R.d1, m2 = R.o2 + rm * R.d2;
+    const double b0 = m0 - (R.p0 - 1.0), a0 = R.p0 - m0;
+    const double b1 = m1 - (R.p1 - 1.0), a1 = R.p1 - m1;
+    const double b2 = m2 - (R.p2 - 1.0), a2 = R.p2 - m2;
+    const double e0 = fmin(b0, a0), e1 = fmin(b1, a1), e2 = fmin(b2, a2);
+    f1 = e1 < e0;
+    const double e01 = fmin(e0, e1);
+    f2 = e2 < e01;
+    dedge = fmin(e01, e2);
     near = dedge < 0.5 * lpix;
-    if (near && (CORR == NRT_CORR_CONSERVATIVE || CORR == NRT_CORR_NAIVE)) {
-      // the neighbour differs from the cell in the face's axis only
-      const int i_f = fax == 0 ? R.i0 : (fax == 1 ? R.i1 : R.i2);
-      const int j_f = i_f + fdir;
-      if (!open_box || !(j_f < 0 || j_f >= n)) {
-        const int w_f = open_box ? i_f : (fax == 0 ? R.w0 : (fax == 1 ? R.w1 : R.w2));
-        const int v_f = open_box ? j_f : wrap_step(w_f, fdir, n);
-        // n^2 <= 2^24 fits 32 bits: one 32 x 32 -> 64 signed multiply
-        const int32_t stride = fax == 0 ? 1 : (fax == 1 ? n : n * n);
-        c2 = c + int64_t(v_f - w_f) * int64_t(stride);
-        neighbour = true;
+    if constexpr (neighbours) {
+      neighbour = near;
+      const bool h0 = b0 < a0, h1 = b1 < a1, h2 = b2 < a2;
+      behind = f2 ? h2 : (f1 ? h1 : h0);
+      const int st_f = f2 ? st2 : (f1 ? st1 : st0);
+      c2 = near ? c + Idx(behind ? -st_f : st_f) : c;
+    }
+  }
+  // cells on the box's boundary layer, where a step or a neighbour wraps or
+  // leaves: from the planes themselves, without branches.  Rare on large
+  // grids (6/n of the cells), so the other cells carry no wrapped coordinates.
+  bool escaped = false;
+  if (!(tn <= R.s_in)) {
+    ArgsK& F = fresh_args();
+    const double n = double(F.n), inv_n = F.inv_n;
+    double h0 = box_plane(R.p0, n, inv_n), h1 = box_plane(R.p1, n, inv_n),
+           h2 = box_plane(R.p2, n, inv_n);
+    // cells ahead of this one: 0 in the last before the box plane
+    double g0 = h0 - R.p0, g1 = h1 - R.p1, g2 = h2 - R.p2;
+    if constexpr (neighbours) {
+      const double g = f2 ? g2 : (f1 ? g1 : g0);
+      if (near && g == (behind ? n - 1.0 : 0.0)) {
+        neighbour = PERIODIC;
+        const int st_f = f2 ? st2 : (f1 ? st1 : st0);
+        const Idx whole = Idx(st_f) * Idx(F.n);
+        c2 = !PERIODIC ? c : (behind ? c2 + whole : c2 - whole);
       }
     }
-    // requested by every lane, whether or not it needs a neighbour, so the
-    // load is never skipped by a branch and the wait for this cell's word
-    // below can leave it in flight
-    if constexpr (CORR == NRT_CORR_CONSERVATIVE || CORR == NRT_CORR_NAIVE)
-      raw2_64 = A.a64[neighbour ? c2 : c];
+    const double g = x2 ? g2 : (x1 ? g1 : g0);
+    const bool over = g == 0.0;
+    escaped = !PERIODIC && over;
+    if (over) cn = PERIODIC ? cn - Idx(st_x) * Idx(F.n) : c;  // one that left reads its last cell
+    // the new cell's distances and planes
+    const double up = over ? n : 0.0, gx = over ? n - 1.0 : g - 1.0;
+    g0 = x1 || x2 ? g0 : gx;
+    g1 = x1 && !x2 ? gx : g1;
+    g2 = x2 ? gx : g2;
+    h0 += x1 || x2 ? 0.0 : up;
+    h1 += x1 && !x2 ? up : 0.0;
+    h2 += x2 ? up : 0.0;
+    R.s_in = inner_length(R, g0, g1, g2, h0, h1, h2, n);
+  }
+  // requested by every lane, whether or not it needs a neighbour, so the
+  // load is never skipped by a branch and the wait for this cell's word
+  // below can leave it in flight
+  auto l2 = l1;
+  if constexpr (neighbours) {
+    raw2_64 = A.a64[c2];
+    l2 = tab.look(c2);
   }
 
   // ---- segment physics (Eq. lut_eqn, Eq. optical_depth) ----
@@ -564,16 +669,12 @@ __device__ int ray_step(RayState& R, const MarchArgs& A, const LineTable<V>& tab
     const float em = dtau < 0.125f ? poly : 1.0f - e;
     // transmitted fraction in FP64: the absorbed part for weak absorption,
     // the surviving part for strong absorption (where em rounds towards 1)
-    double dT, Tn;
-    if (em < 0.5f) {
-      dT = R.T * double(em);
-      Tn = R.T - dT;
-    } else {
-      Tn = R.T * double(e);
-      dT = R.T - Tn;
-    }
+    const bool weak = em < 0.5f;
+    const double part = R.T * double(weak ? em : e);
+    const double rest = R.T - part;
+    const double dT = weak ? part : rest;
     const float Tf = float(R.T);
-    R.T = Tn;
+    R.T = weak ? rest : part;
     acc.absorbed = fma(R.L, dT, acc.absorbed);
     // an absorber below FP32's normal range takes the thin limit, which is
     // exact there
@@ -589,47 +690,27 @@ __device__ int ray_step(RayState& R, const MarchArgs& A, const LineTable<V>& tab
     R.tau += dtau64;
   }
 
-  // ---- table claims, in flight during the advance ----
-  const auto cl1 = tab.claim(c);
-  typename LineTable<V>::Claim cl2{0u, 0u, 0u};
-  if (neighbour) cl2 = tab.claim(c2);
+  // ---- claims of new lines, in flight during the advance ----
+  tab.claim(l1, true, inserted);
+  if constexpr (neighbours) tab.claim(l2, neighbour, inserted);
 
-  // ---- advance one cell: step the winning axis (its component is nonzero)
-  // and recompute its next plane crossing, without diverging on the axis ----
+  // ---- advance one cell; the next cell's absorber is consumed by the next
+  // step ----
   R.s = tn;
-  {
-    // the winning axis's fields by two selects each (32-bit selects, cheaper
-    // than masked FP64 sums)
-    const bool a0 = ax == 0, a1 = ax == 1;
-    const double o_a = a0 ? R.o0 : (a1 ? R.o1 : R.o2);
-    const double d_a = a0 ? R.d0 : (a1 ? R.d1 : R.d2);
-    const int st_a = d_a > 0.0 ? 1 : -1;
-    const int i_a = (a0 ? R.i0 : (a1 ? R.i1 : R.i2)) + st_a;
-    const int w_a = open_box ? i_a : wrap_step(a0 ? R.w0 : (a1 ? R.w1 : R.w2), st_a, n);
-    const double t_a = (double(st_a > 0 ? i_a + 1 : i_a) - o_a) / d_a;
-    R.i0 = ax == 0 ? i_a : R.i0;
-    R.i1 = ax == 1 ? i_a : R.i1;
-    R.i2 = ax == 2 ? i_a : R.i2;
-    R.w0 = ax == 0 ? w_a : R.w0;
-    R.w1 = ax == 1 ? w_a : R.w1;
-    R.w2 = ax == 2 ? w_a : R.w2;
-    R.t0 = ax == 0 ? t_a : R.t0;
-    R.t1 = ax == 1 ? t_a : R.t1;
-    R.t2 = ax == 2 ? t_a : R.t2;
-  }
+  R.p0 += x1 || x2 ? 0.0 : 1.0;
+  R.p1 += x1 && !x2 ? 1.0 : 0.0;
+  R.p2 += x2 ? 1.0 : 0.0;
+  R.c = cn;
+  R.a64 = A.a64[cn];
   acc.segments += 1;
-  const bool escaped = open_box &&
-      (R.i0 < 0 || R.i0 >= n || R.i1 < 0 || R.i1 >= n || R.i2 < 0 || R.i2 >= n);
-  // absorber of the next cell, consumed by the next step (a ray that left
-  // the open box reads its last cell's instead)
-  R.a64 = A.a64[escaped ? c : cell_index(R.w0, R.w1, R.w2, n)];
 
   // ---- overlap correction values (the decision above is FP64; the factor
   // is FP32 in the mixed path) ----
   using R_t = typename std::conditional<MIXED, float, double>::type;
   R_t fc = R_t(1);
   bool secondary = false;
-  if (near) {
+  float raw2_32 = 0.0f;
+  if constexpr (CORR != NRT_CORR_NONE) {
     const bool usable = neighbour && !__builtin_signbit(raw2_64);
     // the mixed path's FP32 neighbour absorber, floored at the smallest
     // normal so that its reciprocal stays finite
@@ -638,32 +719,34 @@ __device__ int ray_step(RayState& R, const MarchArgs& A, const LineTable<V>& tab
     if constexpr (MIXED)
       f = 0.5f + float(dedge) * __builtin_amdgcn_rcpf(float(lpix));
     else
-      f = 0.5 + dedge / lpix;
+      f = near ? 0.5 + dedge / lpix : 1.0;
     if constexpr (CORR == NRT_CORR_LINEAR) {
-      fc = f;
+      fc = near ? f : R_t(1);
     } else if constexpr (CORR == NRT_CORR_SQUARED) {
-      fc = f * f;
+      fc = near ? f * f : R_t(1);
     } else if constexpr (CORR == NRT_CORR_CONSERVATIVE) {
-      if (usable) fc = f;
+      fc = usable ? f : R_t(1);
       secondary = usable;
     } else {  // NAIVE
-      fc = f;
+      fc = near ? f : R_t(1);
       secondary = usable;
     }
   }
 
   // ---- deposit ----
-  inserted += LineTable<V>::took(cl1) ? 1 : 0;
-  if (neighbour) inserted += LineTable<V>::took(cl2) ? 1 : 0;
   if constexpr (MIXED) {
-    inserted += tab.deposit(cl1, c, fc * G32);
-    if (secondary)
-      inserted += tab.deposit(cl2, c2, ((1.0f - fc) * (a32 * __builtin_amdgcn_rcpf(raw2_32))) * G32);
+    tab.deposit(l1, c, V(fc * G32), true, true, inserted);
+    if constexpr (neighbours)
+      tab.deposit(l2, c2, V(((1.0f - fc) * (a32 * __builtin_amdgcn_rcpf(raw2_32))) * G32),
+                  neighbour, secondary, inserted);
   } else {
-    inserted += tab.deposit(cl1, c, fc * G64);
-    if (secondary) inserted += tab.deposit(cl2, c2, ((1.0 - fc) * (a64 / raw2_64)) * G64);
+    tab.deposit(l1, c, V(fc * G64), true, true, inserted);
+    if constexpr (neighbours) {
+      double v2 = 0.0;
+      if (secondary) v2 = ((1.0 - fc) * (a64 / raw2_64)) * G64;
+      tab.deposit(l2, c2, V(v2), neighbour, secondary, inserted);
+    }
   }
-
   return escaped ? kEscaped : kGoOn;
 }
 
@@ -700,22 +783,21 @@ __device__ __forceinline__ void push_pending(unsigned long long* count, const Ra
 // launch's range (its first by position, the rest from a shared counter),
 // refills idle lanes from its run once A.refill_min of them are idle,
 // advances every busy lane by up to 8 cells per iteration, and folds its
-// LDS table into Gamma when a quarter full.  A lane whose ray splits keeps the
-// children's start state in registers; the wavefront appends the children of
+// LDS table into Gamma when enough slots are taken.  A lane whose ray splits
+// keeps the children's start state in registers; the wavefront appends the children of
 // all pending splits to the next level's queue with one atomicAdd once every
 // lane holds one (or a pending lane splits again, or the wavefront is done):
 // fewer same-address atomics than a push at 32 (1024^3: +1.3 % mixed, +4 %
 // FP64).
 // The mixed march is held to 128 VGPRs, which keeps 4 waves per SIMD as its
-// LDS allows (it fits with no VGPR spills), except the open-box
-// polychromatic one, which would spill under that cap; it and the FP64
-// march are left to the compiler (3 waves per SIMD).
-template <bool MIXED, int CORR, bool PERIODIC, bool POLY>
+// LDS allows (spilling at most a few budget words that the loop does not
+// touch), except the open-box polychromatic one, which would spill more under
+// that cap; it and the FP64 march are held to 168 (3 waves per SIMD).
+template <bool MIXED, int CORR, bool PERIODIC, bool POLY, typename V, typename Idx>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu((MIXED && (PERIODIC || !POLY)) ? 4 : 1, 8))) void k_march(
+__attribute__((amdgpu_waves_per_eu((MIXED && (PERIODIC || !POLY)) ? 4 : 3, 8))) void k_march(
     MarchArgs A) {
   if (A.skip && *A.skip) return;  // a replayed pass after its iteration stopped
-  using V = typename std::conditional<MIXED, float, double>::type;
   // per-wavefront deposit tables, reused for the budget reduction at the end
   using Tab = LineTable<V>;
   __shared__ __align__(16) unsigned char lds[kWaves * Tab::kWaveBytes];
@@ -724,13 +806,17 @@ __attribute__((amdgpu_waves_per_eu((MIXED && (PERIODIC || !POLY)) ? 4 : 1, 8))) 
   uint32_t* key = reinterpret_cast<uint32_t*>(lds) + wave * Tab::kLines;
   V* val = reinterpret_cast<V*>(lds + kWaves * Tab::kLines * sizeof(uint32_t)) +
            wave * Tab::kLines * kLine;
-  const Tab tab{key, val, A.lds_keys_fit != 0};
+  uint8_t* list = lds + kWaves * Tab::kLines * (sizeof(uint32_t) + kLine * sizeof(V)) +
+                  wave * Tab::kLines;
+  uint32_t mul = sizeof(V) == 4 ? A.line_mul[0] : A.line_mul[1];
+  asm volatile("" : "+s"(mul));
+  const Tab tab{key, val, list, mul};
   for (int q = lane; q < Tab::kLines; q += 64) key[q] = kEmpty;
   for (int q = lane; q < Tab::kLines * kLine; q += 64) val[q] = V(0);
   __builtin_amdgcn_wave_barrier();
 
   LaneAcc acc;
-  RayState R;
+  RayState<Idx> R;
   bool busy = false;
   // pending split of this lane: children start state
   bool pend = false;
@@ -741,17 +827,17 @@ __attribute__((amdgpu_waves_per_eu((MIXED && (PERIODIC || !POLY)) ? 4 : 1, 8))) 
     const int64_t k = int64_t(*A.count_src);
     total = k < A.in_cap ? k : A.in_cap;
   }
-  // Wavefront w starts with rays [w claim, (w+1) claim) of the launch's range
+  // Wavefront w starts with rays [w run, (w+1) run) of the launch's range
   // without touching the shared counter, which hands out the runs after the
-  // first nwaves * claim.  A wavefront with no first run has nothing to do,
+  // first nwaves * run.  A wavefront with no first run has nothing to do,
   // so the idle part of a persistent grid (small levels) issues no atomics.
-  const int64_t claim = A.claim;
-  const int64_t first_runs = int64_t(gridDim.x) * kWaves * claim;
+  const int64_t run = A.claim;
+  const int64_t first_runs = int64_t(gridDim.x) * kWaves * run;
   // the run bounds are wavefront-uniform: derive them from a uniform wave
   // index so that they stay in scalar registers
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  int64_t pool = (int64_t(blockIdx.x) * kWaves + wave_u) * claim;
-  int64_t pool_end = pool + claim < total ? pool + claim : total;
+  int64_t pool = (int64_t(blockIdx.x) * kWaves + wave_u) * run;
+  int64_t pool_end = pool + run < total ? pool + run : total;
   bool exhausted = pool >= total;
   if (exhausted) pool = pool_end = 0;
   const StepConst K(A);
@@ -763,13 +849,13 @@ __attribute__((amdgpu_waves_per_eu((MIXED && (PERIODIC || !POLY)) ? 4 : 1, 8))) 
       ArgsK& F = fresh_args();
       if (pool == pool_end) {
         unsigned long long b = 0;
-        if (lane == 0) b = atomicAdd(F.claim_ctr, static_cast<unsigned long long>(claim));
+        if (lane == 0) b = atomicAdd(F.claim_ctr, static_cast<unsigned long long>(run));
         b = read_lane64(b, 0) + static_cast<unsigned long long>(first_runs);
         if (int64_t(b) >= total) {
           exhausted = true;
         } else {
           pool = int64_t(b);
-          pool_end = int64_t(b) + claim < total ? int64_t(b) + claim : total;
+          pool_end = int64_t(b) + run < total ? int64_t(b) + run : total;
         }
       }
       if (!exhausted) {
@@ -1029,38 +1115,56 @@ hipError_t launch_zero_accum(Accum* acc, hipStream_t s, const unsigned long long
 
 namespace {
 
-// the march instantiation for a precision, correction mode, boundary and spectrum
+// The march instantiation for a precision, correction mode, boundary and
+// spectrum, and:
+//  - the sums of the deposit table.  FP64, except in the mixed path's first
+//    levels: LDS adds FP32 lane by lane (3.1 cycles each), so FP64 sums are
+//    faster as well as more exact (128^3 mixed, levels 5 and up: see
+//    LineTable), but the cells next to a source, which take their few
+//    deposits from rays of levels 0..4 (within 4 cells), keep the FP32 sums
+//    that set their values; those levels are a small part of any pass whose
+//    rays reach further;
+//  - the cell index: 32 bits while n^3 <= 2^32 (n <= 1625), else 64.
 using MarchKernel = void (*)(MarchArgs);
+constexpr int kFirstWideSumLevel = 5;
 
-template <bool MIXED, bool PERIODIC, bool POLY>
+template <bool MIXED, bool PERIODIC, bool POLY, typename V, typename Idx>
 MarchKernel march_for_corr(int corr) {
   switch (corr) {
-    case NRT_CORR_NONE: return k_march<MIXED, NRT_CORR_NONE, PERIODIC, POLY>;
-    case NRT_CORR_LINEAR: return k_march<MIXED, NRT_CORR_LINEAR, PERIODIC, POLY>;
-    case NRT_CORR_SQUARED: return k_march<MIXED, NRT_CORR_SQUARED, PERIODIC, POLY>;
-    case NRT_CORR_NAIVE: return k_march<MIXED, NRT_CORR_NAIVE, PERIODIC, POLY>;
-    default: return k_march<MIXED, NRT_CORR_CONSERVATIVE, PERIODIC, POLY>;
+    case NRT_CORR_NONE: return k_march<MIXED, NRT_CORR_NONE, PERIODIC, POLY, V, Idx>;
+    case NRT_CORR_LINEAR: return k_march<MIXED, NRT_CORR_LINEAR, PERIODIC, POLY, V, Idx>;
+    case NRT_CORR_SQUARED: return k_march<MIXED, NRT_CORR_SQUARED, PERIODIC, POLY, V, Idx>;
+    case NRT_CORR_NAIVE: return k_march<MIXED, NRT_CORR_NAIVE, PERIODIC, POLY, V, Idx>;
+    default: return k_march<MIXED, NRT_CORR_CONSERVATIVE, PERIODIC, POLY, V, Idx>;
   }
 }
 
-template <bool POLY>
-MarchKernel march_for_spectrum(const nrt_grid_desc& d) {
-  if (d.precision == NRT_MIXED)
-    return d.periodic ? march_for_corr<true, true, POLY>(d.corr)
-                      : march_for_corr<true, false, POLY>(d.corr);
-  return d.periodic ? march_for_corr<false, true, POLY>(d.corr)
-                    : march_for_corr<false, false, POLY>(d.corr);
+template <bool MIXED, typename V, typename Idx>
+MarchKernel march_for(const nrt_grid_desc& d) {
+  if (d.spectrum != NRT_SPEC_MONO)
+    return d.periodic ? march_for_corr<MIXED, true, true, V, Idx>(d.corr)
+                      : march_for_corr<MIXED, false, true, V, Idx>(d.corr);
+  return d.periodic ? march_for_corr<MIXED, true, false, V, Idx>(d.corr)
+                    : march_for_corr<MIXED, false, false, V, Idx>(d.corr);
 }
 
-MarchKernel march_kernel(const nrt_grid_desc& d) {
-  return d.spectrum != NRT_SPEC_MONO ? march_for_spectrum<true>(d)
-                                     : march_for_spectrum<false>(d);
+bool wide_sums(const nrt_grid_desc& d, int level) {
+  return d.precision != NRT_MIXED || level >= kFirstWideSumLevel;
+}
+
+MarchKernel march_kernel(const nrt_grid_desc& d, int level) {
+  const bool wide = int64_t(d.n) * d.n * d.n > (int64_t(1) << 32);
+  if (d.precision != NRT_MIXED)
+    return wide ? march_for<false, double, int64_t>(d) : march_for<false, double, uint32_t>(d);
+  if (!wide_sums(d, level))
+    return wide ? march_for<true, float, int64_t>(d) : march_for<true, float, uint32_t>(d);
+  return wide ? march_for<true, double, int64_t>(d) : march_for<true, double, uint32_t>(d);
 }
 
 }  // namespace
 
 hipError_t march_blocks_per_cu(const nrt_grid_desc& d, int* blocks) {
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, march_kernel(d), kBlock, 0);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, march_kernel(d, kMaxLevel), kBlock, 0);
 }
 
 // persistent grid: as many blocks as stay resident, or fewer for small launches
@@ -1077,7 +1181,7 @@ hipError_t launch_march_on(const nrt_grid_desc& d, int cu_count, int resident_pe
   // refill once 16 lanes idle amortizes the ray set-up
   a.claim = t.claim > 0 ? t.claim : 128;
   a.refill_min = t.refill_min > 0 ? t.refill_min : 16;
-  hipLaunchKernelGGL(march_kernel(d), dim3(blocks), dim3(kBlock), 0, st, a);
+  hipLaunchKernelGGL(march_kernel(d, a.level), dim3(blocks), dim3(kBlock), 0, st, a);
   return hipGetLastError();
 }
 
