@@ -86,7 +86,7 @@ struct MarchArgs {
   int32_t level;     // HEALPix level of every input ray (-1: injected rays)
   int32_t spawn;     // 1: input ray r is (src_begin + r/12, pix r%12, s 0, w 0/1)
   int32_t refill_min;    // idle lanes that trigger a refill of a wavefront
-  int64_t claim;         // rays a wavefront claims at a time
+  int64_t claim, claim_min;  // most and least rays a wavefront claims at a time
   uint32_t line_mul[2];  // slot hash multipliers of the deposit table, FP32 and FP64 sums
   double h_cm, sigma0, tau_max, s_max, h3;
   double inv_n;      // 1 / n

@@ -779,9 +779,23 @@ __device__ __forceinline__ void push_pending(unsigned long long* count, const Ra
   }
 }
 
-// Persistent march: every wavefront takes runs of A.claim rays of the
-// launch's range (its first by position, the rest from a shared counter),
-// refills idle lanes from its run once A.refill_min of them are idle,
+// Size of a wavefront's next run of rays.  The claims are same-address atomics,
+// about 130 M/s for the device, which bound launches of short rays (39^3, 8
+// cells a ray: runs of 64 / 128 / 256 take 8.5 / 7.1 / 6.6 ms); long runs
+// leave a long tail where rays are long (1024^3, 100 cells a ray: 221 / 234 /
+// 262 ms).  So the run follows the cells that 64 rays of the last one took,
+// within the wavefront's even share of what is left.
+__device__ __forceinline__ int64_t run_size(int64_t cells_per_64, int64_t left, float share,
+                                            int64_t lo, int64_t hi) {
+  const int64_t by_cells = cells_per_64 <= 16 ? 256 : (cells_per_64 <= 32 ? 128 : 64);
+  const int64_t even = int64_t(float(left) * share) & ~int64_t(63);
+  const int64_t r = by_cells < even ? by_cells : even;
+  return r < lo ? lo : (r > hi ? hi : r);
+}
+
+// Persistent march: every wavefront takes runs of rays of the launch's range
+// (its first by position, the rest from a shared counter; their size from
+// run_size), refills idle lanes from its run once A.refill_min of them are idle,
 // advances every busy lane by up to 8 cells per iteration, and folds its
 // LDS table into Gamma when enough slots are taken.  A lane whose ray splits
 // keeps the children's start state in registers; the wavefront appends the children of
@@ -831,8 +845,10 @@ __attribute__((amdgpu_waves_per_eu((MIXED && (PERIODIC || !POLY)) ? 4 : 3, 8))) 
   // without touching the shared counter, which hands out the runs after the
   // first nwaves * run.  A wavefront with no first run has nothing to do,
   // so the idle part of a persistent grid (small levels) issues no atomics.
-  const int64_t run = A.claim;
-  const int64_t first_runs = int64_t(gridDim.x) * kWaves * run;
+  const int64_t nwaves = int64_t(gridDim.x) * kWaves;
+  const float share = 1.0f / float(nwaves);
+  int64_t run = run_size(0, total, 0.25f * share, A.claim_min, A.claim);
+  const int64_t first_runs = nwaves * run;
   // the run bounds are wavefront-uniform: derive them from a uniform wave
   // index so that they stay in scalar registers
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -841,6 +857,7 @@ __attribute__((amdgpu_waves_per_eu((MIXED && (PERIODIC || !POLY)) ? 4 : 3, 8))) 
   bool exhausted = pool >= total;
   if (exhausted) pool = pool_end = 0;
   const StepConst K(A);
+  int iterations = 0;              // since the last claim
   int fill = 0;                    // wavefront-uniform occupied line slots
   for (;;) {
     const uint64_t idle = __ballot(!busy);
@@ -848,6 +865,11 @@ __attribute__((amdgpu_waves_per_eu((MIXED && (PERIODIC || !POLY)) ? 4 : 3, 8))) 
     if (!exhausted && (n_idle >= A.refill_min || n_idle == 64)) {
       ArgsK& F = fresh_args();
       if (pool == pool_end) {
+        // what is left by this wavefront's last run (others may have taken more)
+        const int64_t left = total - (pool > first_runs ? pool : first_runs);
+        run = run_size(int64_t(iterations) * kCellsPerIteration * 64 / run, left, share,
+                       F.claim_min, F.claim);
+        iterations = 0;
         unsigned long long b = 0;
         if (lane == 0) b = atomicAdd(F.claim_ctr, static_cast<unsigned long long>(run));
         b = read_lane64(b, 0) + static_cast<unsigned long long>(first_runs);
@@ -876,6 +898,7 @@ __attribute__((amdgpu_waves_per_eu((MIXED && (PERIODIC || !POLY)) ? 4 : 3, 8))) 
     }
     // a few cells per busy lane between the wavefront's bookkeeping (refill,
     // split pushes, table occupancy); a lane that stops sits out the rest
+    ++iterations;
     int code = kGoOn, inserted = 0;
 #pragma unroll 1
     for (int k = 0; k < kCellsPerIteration && busy; ++k) {
@@ -1175,12 +1198,18 @@ hipError_t launch_march_on(const nrt_grid_desc& d, int cu_count, int resident_pe
   if (t.blocks_per_cu > 0 && t.blocks_per_cu < per_cu) per_cu = t.blocks_per_cu;
   const int blocks = grid_for(rays, kBlock, cu_count * per_cu);
   MarchArgs a = args;
-  // defaults from sweeps of the device-driven pass on the 128^3, 256^3 and
-  // 512^3 workloads: runs of two wavefronts of rays halve the claims of
-  // short-ray workloads without starving waves at the end of a level; a
-  // refill once 16 lanes idle amortizes the ray set-up
-  a.claim = t.claim > 0 ? t.claim : 128;
-  a.refill_min = t.refill_min > 0 ? t.refill_min : 16;
+  // Defaults.  A wavefront that refills only once it has drained keeps its 64
+  // rays in step: neighbouring pixels at one path length, which share lines of
+  // Gamma (5 new ones a step against 10 when it refills at 16 idle lanes; its
+  // children are queued side by side, so the next level's runs are bundles
+  // again).  Measured, refill at 16 / 64: 1024^3 mixed 351 / 221 ms, 128^3
+  // mixed 12.6 / 10.8, FP64 15.7 / 14.2, blackbody 35.7 / 26.8, 256^3 11.5 /
+  // 10.4.  Launches with FP32 sums keep the 16 lanes and 128 rays that their
+  // sums' order follows.
+  const bool wide = wide_sums(d, a.level);
+  a.refill_min = t.refill_min > 0 ? t.refill_min : (wide ? 64 : 16);
+  a.claim = t.claim > 0 ? t.claim : (wide ? 256 : 128);
+  a.claim_min = t.claim > 0 || !wide ? a.claim : 64;
   hipLaunchKernelGGL(march_kernel(d, a.level), dim3(blocks), dim3(kBlock), 0, st, a);
   return hipGetLastError();
 }
