@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <system_error>
 #include <thread>
 
 #include "healpix.h"
@@ -376,37 +377,77 @@ nrt_status trace_pass(nrt_ctx* c, double* gamma, nrt_budget* out) {
   return NRT_OK;
 }
 
-// The direction table of levels 0..c->lay.dir_levels, computed on the host
-// with the C library's sincos on the pixelisation's correctly rounded
-// geometry, and copied once.
+// fn(lo, hi) over [0, count) on up to 16 threads; on this one alone below
+// `least` items a thread, and for a thread that cannot be started
+template <typename Fn>
+void over_threads(int64_t count, int64_t least, Fn fn) {
+  const int64_t most = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+  const int64_t nt = std::max<int64_t>(1, std::min(most, count / least));
+  std::thread th[16];
+  for (int64_t t = 1; t < nt; ++t) {
+    try {
+      th[t] = std::thread(fn, count * t / nt, count * (t + 1) / nt);
+    } catch (const std::system_error&) {
+      fn(count * t / nt, count * (t + 1) / nt);
+    }
+  }
+  fn(int64_t(0), count / nt);
+  for (auto& x : th)
+    if (x.joinable()) x.join();
+}
+
+// The direction table of levels 0..c->lay.dir_levels.  Its cosines and sines
+// are the C library's, computed on the host; the pixels of all levels share
+// 4^top / 2 azimuths (one for 32 pixels), so the host evaluates those and the
+// device forms the vectors from them by the same IEEE operations (128^3,
+// levels 0..9: 2 ms, where the host took 30 for the vectors and their copy).
+// Workspaces whose scratch does not hold the azimuths (levels past 9 on grids
+// below 128^3) take the vectors from the host.
 nrt_status fill_direction_table(nrt_ctx* c) {
-  const int64_t total = nrt::dir_table_offset(c->lay.dir_levels + 1);
+  const int top = c->lay.dir_levels;
+  const int64_t azimuths = nrt::hp_azimuth_count(top);
+  const bool on_device = size_t(azimuths) * 16 <= c->scratch_bytes;
+  const int64_t total = nrt::dir_table_offset(top + 1);
   std::vector<double> tab;
   try {
-    tab.resize(size_t(total) * 3);
+    tab.resize(on_device ? size_t(azimuths) * 2 : size_t(total) * 3);
+    if (on_device) {
+      over_threads(azimuths, 8192, [&](int64_t lo, int64_t hi) {
+        // ring of entry lo: the largest nr with (nr - 1)(nr - 2) / 2 <= lo
+        int nr = int(1.5 + std::sqrt(2.0 * double(lo) + 0.25));
+        while (nrt::hp_azimuth_index(nr, 1) > lo) --nr;
+        while (nrt::hp_azimuth_index(nr + 1, 1) <= lo) ++nr;
+        int k = int(lo - nrt::hp_azimuth_index(nr, 1)) + 1;
+        for (int64_t q = lo; q < hi; ++q) {
+          ::sincos(nrt::hp_azimuth(nr, k), &tab[size_t(2 * q + 1)], &tab[size_t(2 * q)]);
+          if (++k >= nr) {
+            ++nr;
+            k = 1;
+          }
+        }
+      });
+    } else {
+      for (int l = 0; l <= top; ++l) {
+        const int64_t first = nrt::dir_table_offset(l);
+        over_threads(12 * (int64_t(1) << (2 * l)), 4096, [&](int64_t lo, int64_t hi) {
+          for (int64_t p = lo; p < hi; ++p) {
+            double* d = tab.data() + 3 * (first + p);
+            const nrt::HpAngle a = nrt::healpix_angle(l, uint32_t(p));
+            double ca = 1.0, sa = 0.0;
+            if (a.fold >= 2) ::sincos(a.ang, &sa, &ca);
+            nrt::healpix_vector(a, ca, sa, d[0], d[1], d[2]);
+          }
+        });
+      }
+    }
   } catch (const std::bad_alloc&) {
     return fail(c, NRT_ERR_NOMEM, "host memory for the direction table");
   }
-  const int nt = int(std::max(1u, std::min(16u, std::thread::hardware_concurrency())));
-  auto work = [&](int t) {
-    for (int l = 0; l <= c->lay.dir_levels; ++l) {
-      const int64_t first = nrt::dir_table_offset(l), npix = 12 * (int64_t(1) << (2 * l));
-      const int64_t lo = npix * t / nt, hi = npix * (t + 1) / nt;
-      for (int64_t p = lo; p < hi; ++p) {
-        double* d = tab.data() + 3 * (first + p);
-        const nrt::HpAngle a = nrt::healpix_angle(l, uint32_t(p));
-        double ca = 1.0, sa = 0.0;
-        if (a.fold >= 2) ::sincos(a.ang, &sa, &ca);
-        nrt::healpix_vector(a, ca, sa, d[0], d[1], d[2]);
-      }
-    }
-  };
-  std::vector<std::thread> th;
-  for (int t = 1; t < nt; ++t) th.emplace_back(work, t);
-  work(0);
-  for (auto& x : th) x.join();
-  HIP_OR_FAIL(c, hipMemcpyAsync(c->dirs, tab.data(), tab.size() * sizeof(double),
-                                hipMemcpyHostToDevice, c->stream));
+  double* to = on_device ? reinterpret_cast<double*>(c->scratch) : c->dirs;
+  if (!tab.empty())
+    HIP_OR_FAIL(c, hipMemcpyAsync(to, tab.data(), tab.size() * sizeof(double),
+                                  hipMemcpyHostToDevice, c->stream));
+  if (on_device) HIP_OR_FAIL(c, nrt::launch_directions(top, to, c->dirs, c->stream));
   HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
   return NRT_OK;
 }

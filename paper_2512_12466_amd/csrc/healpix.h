@@ -28,11 +28,24 @@ __host__ __device__ inline uint32_t hp_compact(uint32_t v) {
   return v;
 }
 
+// The folded azimuths pi k / (4 nr), 1 <= k < nr, in the order of nr: a level's
+// rings have nr <= 2^level, so its azimuths are a prefix, 4^level / 2 entries.
+__host__ __device__ inline double hp_azimuth(int nr, int k) {
+  return (3.14159265358979323846 * double(k)) / double(4 * nr);
+}
+__host__ __device__ inline int64_t hp_azimuth_index(int nr, int k) {
+  return int64_t(nr - 1) * (nr - 2) / 2 + (k - 1);
+}
+__host__ __device__ inline int64_t hp_azimuth_count(int level) {
+  return hp_azimuth_index((1 << level) + 1, 1);
+}
+
 // Pixel geometry without the trigonometry: z, sin(theta), and the azimuth
 // folded into [0, pi/4] as ang = pi k / (4 nr) with the unfolding rule.
 struct HpAngle {
   double z, st;
   double ang;  // folded azimuth (used when fold >= 2)
+  int nr, k;   // its ring and step
   int quad;    // quadrant of the azimuth
   int fold;    // 0: (c, s) = (1, 0); 1: c = s = sqrt(1/2); 2: (cos, sin) of ang; 3: swapped
 };
@@ -74,14 +87,16 @@ __host__ __device__ inline HpAngle healpix_angle(int level, uint32_t pix) {
   // azimuth within the quadrant folded into [0, pi/4]: one cos and one sin,
   // swapped for the upper half
   a.ang = 0.0;
+  a.nr = nr;
+  a.k = 0;
   if (rem == 0) {
     a.fold = 0;
   } else if (rem == nr) {
     a.fold = 1;
   } else {
     const bool low = rem < nr;
-    const int k = low ? rem : 2 * nr - rem;
-    a.ang = (3.14159265358979323846 * double(k)) / double(4 * nr);
+    a.k = low ? rem : 2 * nr - rem;
+    a.ang = hp_azimuth(nr, a.k);
     a.fold = low ? 2 : 3;
   }
   return a;

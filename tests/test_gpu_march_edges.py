@@ -45,3 +45,23 @@ def test_tiny_boxes(gpu, orc, n, periodic, corr):
         assert np.abs(got[mask] / ref[mask] - 1).max() <= tol, prec
         for k in ("absorbed", "escaped", "truncated"):
             assert abs(b[k] - rb[k]) <= (1e-10 if prec == 0 else 1e-6) * rb["emitted"], (prec, k)
+
+
+@pytest.mark.parametrize("n,l_max", [(4, 0), (4, 1), (4, 9), (4, 10), (128, 11)])
+def test_direction_table_levels(gpu, orc, n, l_max):
+    """The direction table formed on the device (its azimuths fit the scratch
+    space) and the one formed on the host (4^3 with levels past 9) hold the
+    oracle's directions bit for bit at every level."""
+    import torch
+    one = torch.ones((n, n, n), dtype=torch.float64, device="cuda:0")
+    ctx = gpu.init_grid(gpu.make_desc(n, 1e20, l_max=l_max), one, 0 * one, device="cuda:0",
+                        max_sources=1, ray_capacity=4096)
+    g = np.random.default_rng(5)
+    for level in range(l_max + 1):
+        npix = 12 * 4 ** level
+        for first in {0, max(0, npix - 40), npix // 2, *g.integers(0, npix, 12).tolist()}:
+            count = min(40, npix - first)
+            ref = np.array([orc.pix2vec_nest(level, p) for p in range(first, first + count)])
+            np.testing.assert_array_equal(ctx.healpix_dirs(level, first, count), ref,
+                                          err_msg=str((level, first)))
+    ctx.destroy()
