@@ -803,13 +803,14 @@ __device__ __forceinline__ int64_t run_size(int64_t cells_per_64, int64_t left, 
 // lane holds one (or a pending lane splits again, or the wavefront is done):
 // fewer same-address atomics than a push at 32 (1024^3: +1.3 % mixed, +4 %
 // FP64).
-// The mixed march is held to 128 VGPRs, which keeps 4 waves per SIMD as its
-// LDS allows (spilling at most a few budget words that the loop does not
-// touch), except the open-box polychromatic one, which would spill more under
-// that cap; it and the FP64 march are held to 168 (3 waves per SIMD).
+// The march is held to 128 VGPRs, which keeps 4 waves per SIMD as its LDS
+// allows: it waits for memory in a third of its cycles, and a fourth wave gains
+// more than the words that spill cost (periodic FP64 23 of them, 128^3: 14.15 ms
+// with 3 waves and none spilled, 13.15 with 4; blackbody, 41: 26.8 and 24.7).
+// Only the open-box polychromatic FP64 one is faster with 3 (96^3: 1.27 / 1.41).
 template <bool MIXED, int CORR, bool PERIODIC, bool POLY, typename V, typename Idx>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu((MIXED && (PERIODIC || !POLY)) ? 4 : 3, 8))) void k_march(
+__attribute__((amdgpu_waves_per_eu((MIXED || PERIODIC || !POLY) ? 4 : 3, 8))) void k_march(
     MarchArgs A) {
   if (A.skip && *A.skip) return;  // a replayed pass after its iteration stopped
   // per-wavefront deposit tables, reused for the budget reduction at the end
