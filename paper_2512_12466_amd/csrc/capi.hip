@@ -214,8 +214,7 @@ nrt_status chunked_pass(nrt_ctx* c, double* gamma, nrt_budget* out) {
   nrt_budget b;
   std::memset(&b, 0, sizeof(b));
   for (double v : c->h_ndot) b.emitted += v;
-  HIP_OR_FAIL(c, nrt::launch_zero(gamma, c->lay.cells, c->cu_count, c->stream));
-  HIP_OR_FAIL(c, nrt::launch_zero_accum(c->acc, c->stream));
+  HIP_OR_FAIL(c, nrt::launch_begin_pass(gamma, c->lay.cells, c->acc, c->cu_count, c->stream));
   c->launches = 0;
   c->march_ms = 0.0;
   PassState ps{&b, gamma};
@@ -274,8 +273,7 @@ hipError_t enqueue_levels(nrt_ctx* c, hipStream_t st, double* gamma,
 }
 
 hipError_t enqueue_device_pass(nrt_ctx* c, hipStream_t st, double* gamma) {
-  hipError_t e = nrt::launch_zero(gamma, c->lay.cells, c->cu_count, st);
-  if (e == hipSuccess) e = nrt::launch_zero_accum(c->acc, st);
+  hipError_t e = nrt::launch_begin_pass(gamma, c->lay.cells, c->acc, c->cu_count, st);
   if (e == hipSuccess) e = enqueue_levels(c, st, gamma, nullptr);
   return e;
 }
@@ -490,10 +488,7 @@ nrt_status capture_rt_graph(nrt_ctx* c, double dt, double alpha, double tol,
   const unsigned long long* skip = &c->rt->done;
   HIP_OR_FAIL(c, hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal));
   hipStream_t s = c->capture_stream;
-  // the accumulators first: the absorber kernel counts invalid cells there
-  hipError_t e = nrt::launch_zero_accum(c->acc, s, skip);
-  if (e == hipSuccess) e = nrt::launch_zero(gamma, c->lay.cells, c->cu_count, s, skip);
-  if (e == hipSuccess) e = nrt::launch_prep_from(c, x_avg, skip, s);
+  hipError_t e = nrt::launch_rt_begin(c, x_avg, gamma, skip, s);
   if (e == hipSuccess) e = enqueue_levels(c, s, gamma, skip);
   if (e == hipSuccess) e = nrt::launch_chem(c, gamma, dt, alpha, tol, x_avg, x_new, s, skip);
   if (e == hipSuccess) e = nrt::launch_rt_check(c->acc, c->rt, threshold, max_iter, s);
@@ -978,8 +973,7 @@ nrt_status nrt_trace_rays_debug(nrt_ctx* c, int64_t k, const double* origin, con
     b.rays_per_level[level[r]] += 1;
   }
   b.rays = uint64_t(k);
-  HIP_OR_FAIL(c, nrt::launch_zero(gamma_out, c->lay.cells, c->cu_count, c->stream));
-  HIP_OR_FAIL(c, nrt::launch_zero_accum(c->acc, c->stream));
+  HIP_OR_FAIL(c, nrt::launch_begin_pass(gamma_out, c->lay.cells, c->acc, c->cu_count, c->stream));
   c->launches = 0;
   if (k > 0) {
     MarchArgs a = base_args(c, gamma_out);

@@ -225,9 +225,11 @@ namespace nrt {
 
 // trace.hip
 hipError_t launch_prep(nrt_ctx* c);
-// the same from another ionized fraction, skipped while *skip is nonzero
-hipError_t launch_prep_from(nrt_ctx* c, const double* x, const unsigned long long* skip,
-                            hipStream_t s);
+// start of a captured radiation-step pass: Gamma and the accumulators cleared,
+// the absorber from x (invalid cells counted in c->rt), skipped while *skip
+// is nonzero
+hipError_t launch_rt_begin(nrt_ctx* c, const double* x, double* gamma,
+                           const unsigned long long* skip, hipStream_t s);
 // absorber from n_H and x, invalid input cells counted in acc->invalid
 hipError_t launch_prep_fields(const double* n_H, const double* x, double n_th, int64_t ncell,
                               double* a64, Accum* acc, int cus, hipStream_t s);
@@ -237,9 +239,9 @@ hipError_t launch_march_on(const nrt_grid_desc& d, int cu_count, int resident_pe
                            hipStream_t st);
 // l0[k] = ndot[k] / 12 on the device
 hipError_t launch_source_rates(const double* ndot, int64_t m, double* l0, hipStream_t s);
-hipError_t launch_zero(double* p, int64_t count, int cus, hipStream_t s,
-                       const unsigned long long* skip = nullptr);
-hipError_t launch_zero_accum(Accum* acc, hipStream_t s, const unsigned long long* skip = nullptr);
+// Gamma and the accumulators cleared for a pass
+hipError_t launch_begin_pass(double* gamma, int64_t count, Accum* acc, int cus, hipStream_t s);
+hipError_t launch_zero_accum(Accum* acc, hipStream_t s);
 // end of a captured radiation-step pass: count it, stop the iteration when
 // at most `threshold` cells changed, at max_iter passes, or on an overflow or
 // invalid input (one thread)

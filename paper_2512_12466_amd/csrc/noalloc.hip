@@ -141,7 +141,7 @@ nrt_status nrt_trace_step_noalloc(const nrt_grid_desc* desc, const double* n_H,
   auto dev_fail = [&](hipError_t e) {
     return fail(NRT_ERR_DEVICE, hipGetErrorString(e));
   };
-  hipError_t e = nrt::launch_zero_accum(acc, s);
+  hipError_t e = nrt::launch_begin_pass(gamma_out, cells, acc, cus, s);
   if (e == hipSuccess)
     e = nrt::launch_prep_fields(n_H, x_ion, desc->n_th, cells, a64, acc, cus, s);
   if (e == hipSuccess && m > 0)
@@ -151,7 +151,6 @@ nrt_status nrt_trace_step_noalloc(const nrt_grid_desc* desc, const double* n_H,
   if (e == hipSuccess && m > 0)
     e = hipMemcpyAsync(src_l0, ndot, size_t(m) * 8, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = nrt::launch_source_rates(src_l0, m, src_l0, s);
-  if (e == hipSuccess) e = nrt::launch_zero(gamma_out, cells, cus, s);
   if (e != hipSuccess) return dev_fail(e);
 
   // the device-driven pass: one launch per HEALPix level, each reading its

@@ -123,7 +123,10 @@ struct LineTable {
   // line slots per wavefront: 37 KiB (FP32 sums) or 34.5 KiB (FP64) per block
   static constexpr int kLog2Lines = sizeof(V) == 4 ? kLog2LinesFp32 : kLog2LinesFp64;
   static constexpr int kLines = 1 << kLog2Lines;
-  static constexpr int kFlushAt = kLines / 4;
+  // slots in use that make a fold, checked every 8 cells (about 35 new lines):
+  // at an eighth (FP64) against a quarter 128^3 mixed takes 10.59 / 10.75 ms; at
+  // three eighths 11.2, at a half 11.9, for probes in a fuller table
+  static constexpr int kFlushAt = sizeof(V) == 4 ? kLines / 4 : kLines / 8;
   static constexpr size_t kWaveBytes =
       kLines * (sizeof(uint32_t) + sizeof(uint8_t) + kLine * sizeof(V));
 
@@ -813,6 +816,21 @@ __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu((MIXED || PERIODIC || !POLY) ? 4 : 3, 8))) void k_march(
     MarchArgs A) {
   if (A.skip && *A.skip) return;  // a replayed pass after its iteration stopped
+  int64_t total = A.end - A.begin;
+  if (A.count_src) {
+    const int64_t k = int64_t(*A.count_src);
+    total = k < A.in_cap ? k : A.in_cap;
+  }
+  // Wavefront w starts with rays [w run, (w+1) run) of the launch's range
+  // without touching the shared counter, which hands out the runs after the
+  // first nwaves * run.  A block with no first run leaves at once: the idle
+  // part of a persistent grid (small and empty levels) clears no tables and
+  // issues no atomics.
+  const int64_t nwaves = int64_t(gridDim.x) * kWaves;
+  const float share = 1.0f / float(nwaves);
+  int64_t run = run_size(0, total, 0.25f * share, A.claim_min, A.claim);
+  const int64_t first_runs = nwaves * run;
+  if (int64_t(blockIdx.x) * kWaves * run >= total) return;
   // per-wavefront deposit tables, reused for the budget reduction at the end
   using Tab = LineTable<V>;
   __shared__ __align__(16) unsigned char lds[kWaves * Tab::kWaveBytes];
@@ -837,19 +855,6 @@ __attribute__((amdgpu_waves_per_eu((MIXED || PERIODIC || !POLY) ? 4 : 3, 8))) vo
   bool pend = false;
   uint32_t p_src = 0, p_pix = 0;
   double p_s = 0.0, p_w = 0.0;
-  int64_t total = A.end - A.begin;
-  if (A.count_src) {
-    const int64_t k = int64_t(*A.count_src);
-    total = k < A.in_cap ? k : A.in_cap;
-  }
-  // Wavefront w starts with rays [w run, (w+1) run) of the launch's range
-  // without touching the shared counter, which hands out the runs after the
-  // first nwaves * run.  A wavefront with no first run has nothing to do,
-  // so the idle part of a persistent grid (small levels) issues no atomics.
-  const int64_t nwaves = int64_t(gridDim.x) * kWaves;
-  const float share = 1.0f / float(nwaves);
-  int64_t run = run_size(0, total, 0.25f * share, A.claim_min, A.claim);
-  const int64_t first_runs = nwaves * run;
   // the run bounds are wavefront-uniform: derive them from a uniform wave
   // index so that they stay in scalar registers
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -974,19 +979,19 @@ __attribute__((amdgpu_waves_per_eu((MIXED || PERIODIC || !POLY) ? 4 : 3, 8))) vo
 // a = (1 - x) n_H with the neighbour flag in the sign bit: a cell is a
 // usable neighbour (Eqs. new_correction / new_secondary) iff n_H >= n_th and
 // a > 0; otherwise -a is stored (-0.0 for a = 0).  Invalid inputs are counted.
+__device__ __forceinline__ bool prep_cell(double nh, double xx, double n_th, double* a64) {
+  const double a = (1.0 - xx) * nh;
+  const bool usable = nh >= n_th && a > 0.0;
+  *a64 = usable ? a : -a;
+  return !(nh >= 0.0) || isinf(nh) || !(xx >= 0.0 && xx <= 1.0);
+}
+
 __global__ void k_prep(const double* __restrict__ n_H, const double* __restrict__ x, double n_th,
-                       int64_t ncell, double* a64, Accum* acc,
-                       const unsigned long long* skip) {
-  if (skip && *skip) return;
+                       int64_t ncell, double* a64, Accum* acc) {
   unsigned long long bad = 0;
   for (int64_t c = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; c < ncell;
-       c += int64_t(gridDim.x) * blockDim.x) {
-    const double nh = n_H[c], xx = x[c];
-    if (!(nh >= 0.0) || isinf(nh) || !(xx >= 0.0 && xx <= 1.0)) ++bad;
-    const double a = (1.0 - xx) * nh;
-    const bool usable = nh >= n_th && a > 0.0;
-    a64[c] = usable ? a : -a;
-  }
+       c += int64_t(gridDim.x) * blockDim.x)
+    bad += prep_cell(n_H[c], x[c], n_th, a64 + c) ? 1 : 0;
   if (bad) atomicAdd(&acc->invalid, bad);
 }
 
@@ -1016,15 +1021,31 @@ __global__ void k_spec_stop(SpecTable t, double tau_max, double hi, double* out)
   *out = hi;
 }
 
-__global__ void k_fill_zero(double* p, int64_t count, const unsigned long long* skip) {
+// Clear Gamma and the accumulators for a pass: one launch, since small passes
+// are launches (about 4 us each) and little else.  With n_H, also the absorber
+// of a radiation step's pass from its ionized fraction (as k_prep); invalid
+// cells are counted in *invalid, which this kernel does not clear.
+__global__ void k_begin_pass(double* gamma, int64_t count, Accum* acc,
+                             const double* __restrict__ n_H, const double* __restrict__ x,
+                             double n_th, double* a64, unsigned long long* invalid,
+                             const unsigned long long* skip) {
   if (skip && *skip) return;
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < count;
-       i += int64_t(gridDim.x) * blockDim.x)
-    p[i] = 0.0;
+  if (blockIdx.x == 0) {
+    unsigned long long* p = reinterpret_cast<unsigned long long*>(acc);
+    for (int i = threadIdx.x; i < int(sizeof(Accum) / sizeof(unsigned long long));
+         i += blockDim.x)
+      p[i] = 0ull;
+  }
+  unsigned long long bad = 0;
+  for (int64_t c = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; c < count;
+       c += int64_t(gridDim.x) * blockDim.x) {
+    gamma[c] = 0.0;
+    if (n_H) bad += prep_cell(n_H[c], x[c], n_th, a64 + c) ? 1 : 0;
+  }
+  if (bad) atomicAdd(invalid, bad);
 }
 
-__global__ void k_zero_accum(Accum* acc, const unsigned long long* skip) {
-  if (skip && *skip) return;
+__global__ void k_zero_accum(Accum* acc) {
   unsigned long long* p = reinterpret_cast<unsigned long long*>(acc);
   const int words = int(sizeof(Accum) / sizeof(unsigned long long));
   for (int i = threadIdx.x; i < words; i += blockDim.x) p[i] = 0ull;
@@ -1103,15 +1124,15 @@ int grid_for(int64_t items, int block, int cap) {
 hipError_t launch_prep_fields(const double* n_H, const double* x, double n_th, int64_t ncell,
                               double* a64, Accum* acc, int cus, hipStream_t s) {
   hipLaunchKernelGGL(k_prep, dim3(grid_for(ncell, 256, cus * 16)), dim3(256), 0, s, n_H, x, n_th,
-                     ncell, a64, acc, nullptr);
+                     ncell, a64, acc);
   return hipGetLastError();
 }
 
-hipError_t launch_prep_from(nrt_ctx* c, const double* x, const unsigned long long* skip,
-                            hipStream_t s) {
-  const int64_t ncell = c->lay.cells;
-  hipLaunchKernelGGL(k_prep, dim3(grid_for(ncell, 256, c->cu_count * 16)), dim3(256), 0, s,
-                     c->n_H, x, c->desc.n_th, ncell, c->a64, c->acc, skip);
+hipError_t launch_rt_begin(nrt_ctx* c, const double* x, double* gamma,
+                           const unsigned long long* skip, hipStream_t s) {
+  const int64_t n = c->lay.cells;
+  hipLaunchKernelGGL(k_begin_pass, dim3(grid_for(n, 256, c->cu_count * 16)), dim3(256), 0, s, gamma,
+                     n, c->acc, c->n_H, x, c->desc.n_th, c->a64, &c->rt->invalid, skip);
   return hipGetLastError();
 }
 
@@ -1139,15 +1160,14 @@ hipError_t launch_spec_stop(const nrt_ctx* c, double* out) {
   return hipGetLastError();
 }
 
-hipError_t launch_zero(double* p, int64_t count, int cus, hipStream_t s,
-                       const unsigned long long* skip) {
-  hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(count, 256, cus * 16)), dim3(256), 0, s, p,
-                     count, skip);
+hipError_t launch_begin_pass(double* gamma, int64_t count, Accum* acc, int cus, hipStream_t s) {
+  hipLaunchKernelGGL(k_begin_pass, dim3(grid_for(count, 256, cus * 16)), dim3(256), 0, s, gamma,
+                     count, acc, nullptr, nullptr, 0.0, nullptr, nullptr, nullptr);
   return hipGetLastError();
 }
 
-hipError_t launch_zero_accum(Accum* acc, hipStream_t s, const unsigned long long* skip) {
-  hipLaunchKernelGGL(k_zero_accum, dim3(1), dim3(256), 0, s, acc, skip);
+hipError_t launch_zero_accum(Accum* acc, hipStream_t s) {
+  hipLaunchKernelGGL(k_zero_accum, dim3(1), dim3(256), 0, s, acc);
   return hipGetLastError();
 }
 
