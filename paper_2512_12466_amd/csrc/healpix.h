@@ -1,8 +1,8 @@
 // HEALPix nested pixel centres (Gorski et al. 2005), the pixelisation along
 // which the paper's rays split (Sec. "Adaptive ray tracing", Fig. raysplit).
-// The geometry is shared by the host, where the context fills its direction
-// table with the C library's sincos, and the march, which evaluates levels
-// past the table with the device's cos and sin.
+// The context's direction table takes the cos and sin of every azimuth from
+// the C library on the host and forms the vectors on the device; the march
+// evaluates levels past the table with the device's cos and sin.
 //
 // pix = face * Ns^2 + ipf with the in-face coordinates interleaved in ipf
 // (ix on even bits, iy on odd bits); ring jr = (face/4 + 2) Ns - ix - iy - 1;

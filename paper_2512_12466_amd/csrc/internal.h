@@ -127,7 +127,6 @@ struct MarchArgs {
   Accum* acc;
 };
 
-// Workspace carve-out (byte offsets into the caller's buffer).
 // HEALPix directions of every pixel of levels 0..kDirTableMaxLevel are kept
 // in a table (24 B per pixel: 1.6 GB at level 11); deeper levels compute them
 constexpr int kDirTableMaxLevel = 11;
@@ -137,6 +136,7 @@ __host__ __device__ inline int64_t dir_table_offset(int level) {
   return 4 * ((int64_t(1) << (2 * level)) - 1);
 }
 
+// Workspace carve-out (byte offsets into the caller's buffer).
 struct Layout {
   size_t n_H, x, a, srcpos, srcl0, srcaux, queues, accum, rt, dirs, spec, scratch, total;
   int64_t cells, max_sources, capacity;

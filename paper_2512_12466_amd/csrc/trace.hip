@@ -15,11 +15,12 @@
 // from the FP64 absorber by the same operations, so the two paths march the
 // same segments and split the same rays.  MIXED = true computes the
 // attenuation, the deposits and the correction factors in FP32 (the
-// neighbour's absorber rounded from its FP64 word) and tracks the
-// transmitted fraction in FP64.  POLY = true integrates the flux
+// neighbour's absorber rounded from its FP64 word), sums the deposits of
+// HEALPix levels 0..4 in FP32 and of the deeper ones in FP64 (template V),
+// and tracks the transmitted fraction in FP64.  POLY = true integrates the flux
 // over a source spectrum with the table of Phi(tau) = -ln F(tau) built at
 // context set-up (spectrum.hip).  The march is instantiated per precision,
-// correction mode, boundary and spectrum.
+// correction mode, boundary, spectrum, type of the sums and of the cell index.
 #include <cfloat>
 #include <cmath>
 #include <type_traits>
