@@ -57,17 +57,17 @@ WORKLOADS = {  # name -> generator in workloads/ (configs 1-5 of the method's te
 # host-driven in chunks of a quarter of a queue, and each chunk launch ends
 # in a tail of long rays, so fewer, larger chunks pay (2^27: 32 GB of queues)
 DEFAULT_CAPACITY = {"late-reion-1024-262144src": 1 << 29}
-# launch parameters (refill_min, claim) that nrt_autotune picked for these
-# workloads on MI355X, for both paths (for the 1024^3 one, whose passes are
-# too long to autotune, the 128^3 workload's pick, measured better by hand);
-# the others keep the library's defaults (16, 128), which it picked for the
-# 256^3 workload.  --tune runs it again, --launch overrides.
+# launch parameters (refill_min, claim) frozen for these workloads; the others
+# keep the library's defaults.  The 128^3 and 512^3 ones date from a march that
+# refilled at 16 idle lanes; --launch 0,0 (the library's own) is faster there
+# now: 128^3 11.88 -> 9.99 ms, 512^3 FP64 7.64 -> 7.23.  --tune picks again,
+# --launch overrides.
 TUNED = {"lognormal-128-64src": (16, 64), "clustered-512-32768src": (16, 256),
          # long rays in bubbles: a run is taken and retired whole (refill only
-         # a drained wavefront; measured 74.7 -> 77.0 Gseg/s on a 256-source pass)
+         # a drained wavefront; a pass takes 7857 ms, 7930 with the library's)
          "late-reion-1024-262144src": (64, 64),
          # a polychromatic pass keeps whole sibling runs alive: refill only a
-         # drained wavefront (measured: 64.1 -> 67.9 Gseg/s mixed)
+         # drained wavefront
          "lognormal-128-64src+spectrum": (64, 64)}
 
 
