@@ -224,13 +224,14 @@ nrt_status nrt_trace_step_async(nrt_ctx* ctx, double* gamma_out, nrt_budget* bud
    n_H, x_ion: device n^3 FP64 (read during the call; invalid values give
    NRT_ERR_ARG after the pass).  pos host m*3, ndot host m, as for
    nrt_add_sources.  ray_capacity: slots per HEALPix level queue, in
-   [64, 2^32].  gamma_out: device n^3 FP64, overwritten.  budget: host,
-   filled on return (the call synchronises hip_stream).  The pass is the
-   device-driven one (one launch per level): NRT_ERR_OVERFLOW when a level
-   does not fit ray_capacity (the budget then reports the rays that
-   fitted); NRT_ERR_NOMEM when the absorber (8 B per cell), the sources
-   (32 B each) and the queues (24 B per slot and level) exceed 64 MiB.  Calls that overlap on one GPU share the array and
-   race.  Messages: nrt_last_error(NULL). */
+   [64, 2^32].  gamma_out: device n^3 FP64, overwritten (it may overlap n_H
+   or x_ion, which are read before it is cleared).  budget: host, filled on
+   return (the call synchronises hip_stream).  The pass is the device-driven
+   one (one launch per level): NRT_ERR_OVERFLOW when a level does not fit
+   ray_capacity (the budget then reports the rays that fitted);
+   NRT_ERR_NOMEM when the absorber (8 B per cell), the sources (32 B each)
+   and the queues (24 B per slot and level) exceed 64 MiB.  Calls that
+   overlap on one GPU share the array and race.  Messages: nrt_last_error(NULL). */
 nrt_status nrt_trace_step_noalloc(const nrt_grid_desc* desc, const double* n_H,
                                   const double* x_ion, int64_t m, const double* pos,
                                   const double* ndot, int64_t ray_capacity, double* gamma_out,

@@ -237,9 +237,10 @@ hipError_t launch_prep_fields(const double* n_H, const double* x, double n_th, i
 hipError_t launch_march_on(const nrt_grid_desc& d, int cu_count, int resident_per_cu,
                            const nrt_tuning& t, const MarchArgs& a, int64_t rays,
                            hipStream_t st);
-// l0[k] = ndot[k] / 12 on the device
-hipError_t launch_source_rates(const double* ndot, int64_t m, double* l0, hipStream_t s);
-// Gamma and the accumulators cleared for a pass
+// l0[k] = ndot[k] / 12 on the device, and the accumulators cleared for a pass
+hipError_t launch_source_rates(const double* ndot, int64_t m, double* l0, Accum* acc,
+                               hipStream_t s);
+// Gamma and, unless acc is NULL, the accumulators cleared for a pass
 hipError_t launch_begin_pass(double* gamma, int64_t count, Accum* acc, int cus, hipStream_t s);
 hipError_t launch_zero_accum(Accum* acc, hipStream_t s);
 // end of a captured radiation-step pass: count it, stop the iteration when

@@ -141,16 +141,18 @@ nrt_status nrt_trace_step_noalloc(const nrt_grid_desc* desc, const double* n_H,
   auto dev_fail = [&](hipError_t e) {
     return fail(NRT_ERR_DEVICE, hipGetErrorString(e));
   };
-  hipError_t e = nrt::launch_begin_pass(gamma_out, cells, acc, cus, s);
-  if (e == hipSuccess)
-    e = nrt::launch_prep_fields(n_H, x_ion, desc->n_th, cells, a64, acc, cus, s);
-  if (e == hipSuccess && m > 0)
-    e = hipMemcpyAsync(src_pos, pos, size_t(m) * 24, hipMemcpyHostToDevice, s);
   // the rates go into their slot as given and are divided by 12 in place on
-  // the device (no host staging buffer)
+  // the device (no host staging buffer); the accumulators are cleared beside
+  // them, ahead of the absorber, which counts invalid cells there.  Gamma is
+  // cleared last: it may lie over n_H or x_ion, and the march reads neither.
+  hipError_t e = hipSuccess;
+  if (m > 0) e = hipMemcpyAsync(src_pos, pos, size_t(m) * 24, hipMemcpyHostToDevice, s);
   if (e == hipSuccess && m > 0)
     e = hipMemcpyAsync(src_l0, ndot, size_t(m) * 8, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = nrt::launch_source_rates(src_l0, m, src_l0, s);
+  if (e == hipSuccess) e = nrt::launch_source_rates(src_l0, m, src_l0, acc, s);
+  if (e == hipSuccess)
+    e = nrt::launch_prep_fields(n_H, x_ion, desc->n_th, cells, a64, acc, cus, s);
+  if (e == hipSuccess) e = nrt::launch_begin_pass(gamma_out, cells, nullptr, cus, s);
   if (e != hipSuccess) return dev_fail(e);
 
   // the device-driven pass: one launch per HEALPix level, each reading its

@@ -1022,21 +1022,23 @@ __global__ void k_spec_stop(SpecTable t, double tau_max, double hi, double* out)
   *out = hi;
 }
 
-// Clear Gamma and the accumulators for a pass: one launch, since small passes
-// are launches (about 4 us each) and little else.  With n_H, also the absorber
-// of a radiation step's pass from its ionized fraction (as k_prep); invalid
-// cells are counted in *invalid, which this kernel does not clear.
+// clear the accumulators (one block)
+__device__ __forceinline__ void clear_accum(Accum* acc) {
+  unsigned long long* p = reinterpret_cast<unsigned long long*>(acc);
+  for (int i = threadIdx.x; i < int(sizeof(Accum) / sizeof(unsigned long long)); i += blockDim.x)
+    p[i] = 0ull;
+}
+
+// Clear Gamma and, unless acc is NULL, the accumulators for a pass: one launch,
+// since small passes are launches (about 4 us each) and little else.  With n_H,
+// also the absorber of a radiation step's pass from its ionized fraction (as
+// k_prep); invalid cells are counted in *invalid, which this kernel does not clear.
 __global__ void k_begin_pass(double* gamma, int64_t count, Accum* acc,
                              const double* __restrict__ n_H, const double* __restrict__ x,
                              double n_th, double* a64, unsigned long long* invalid,
                              const unsigned long long* skip) {
   if (skip && *skip) return;
-  if (blockIdx.x == 0) {
-    unsigned long long* p = reinterpret_cast<unsigned long long*>(acc);
-    for (int i = threadIdx.x; i < int(sizeof(Accum) / sizeof(unsigned long long));
-         i += blockDim.x)
-      p[i] = 0ull;
-  }
+  if (acc && blockIdx.x == 0) clear_accum(acc);
   unsigned long long bad = 0;
   for (int64_t c = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; c < count;
        c += int64_t(gridDim.x) * blockDim.x) {
@@ -1046,11 +1048,7 @@ __global__ void k_begin_pass(double* gamma, int64_t count, Accum* acc,
   if (bad) atomicAdd(invalid, bad);
 }
 
-__global__ void k_zero_accum(Accum* acc) {
-  unsigned long long* p = reinterpret_cast<unsigned long long*>(acc);
-  const int words = int(sizeof(Accum) / sizeof(unsigned long long));
-  for (int i = threadIdx.x; i < words; i += blockDim.x) p[i] = 0ull;
-}
+__global__ void k_zero_accum(Accum* acc) { clear_accum(acc); }
 
 __global__ void k_healpix(int level, int64_t first, int64_t count, double* out) {
   const int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -1257,17 +1255,19 @@ hipError_t launch_march(const nrt_ctx* c, const MarchArgs& args, int64_t rays, h
 
 namespace {
 // l0[k] = ndot[k] / 12, the rate of a level-0 ray (a correctly rounded
-// division, as on the host)
-__global__ void k_source_rates(const double* ndot, int64_t m, double* l0) {
+// division, as on the host); clears the accumulators for a pass
+__global__ void k_source_rates(const double* ndot, int64_t m, double* l0, Accum* acc) {
+  if (blockIdx.x == 0) clear_accum(acc);
   for (int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; k < m;
        k += int64_t(gridDim.x) * blockDim.x)
     l0[k] = ndot[k] / 12.0;
 }
 }  // namespace
 
-hipError_t launch_source_rates(const double* ndot, int64_t m, double* l0, hipStream_t s) {
-  if (m <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_source_rates, dim3(grid_for(m, 256, 1024)), dim3(256), 0, s, ndot, m, l0);
+hipError_t launch_source_rates(const double* ndot, int64_t m, double* l0, Accum* acc,
+                               hipStream_t s) {
+  hipLaunchKernelGGL(k_source_rates, dim3(grid_for(m, 256, 1024)), dim3(256), 0, s, ndot, m, l0,
+                     acc);
   return hipGetLastError();
 }
 

@@ -75,3 +75,31 @@ def test_noalloc_rejects_what_does_not_fit(gpu):
         gpu.trace_step_noalloc(gpu.make_desc(n, 1e20, spectrum=1, spec_param=5e4), f + 1e-3, f,
                                [[1.0, 1.0, 1.0]], [1e49], g, 4096)
     assert e.value.status == 1
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("over", ["x", "n_H", "shifted x"])
+def test_noalloc_gamma_over_an_input(gpu, prec, over):
+    """Gamma may take the place of an input field, wholly or shifted by some
+    cells: the absorber is formed before Gamma is cleared.  Against the same
+    call with a buffer of its own, under the bar between two passes."""
+    import torch
+    n, m = 24, 2
+    nH, x, pos, ndot, h = case(n, 3, m)
+    dev = torch.device("cuda:0")
+    desc = gpu.make_desc(n, h, periodic=True, n_min_ray=4.0, l_max=5, tau_max=30.0, n_th=4e-4,
+                         precision=prec)
+    cap = 1 << 16  # above 12 m 4^5 rays
+    gamma = torch.empty((n, n, n), dtype=torch.float64, device=dev)
+    nh_t, x_t = torch.from_numpy(nH).to(dev), torch.from_numpy(x).to(dev)
+    b_ref = gpu.trace_step_noalloc(desc, nh_t, x_t, pos, ndot, gamma, cap)
+    ref = gamma.cpu().numpy()
+    out = x_t if over == "x" else nh_t
+    if over == "shifted x":
+        room = torch.empty(n ** 3 + 1000, dtype=torch.float64, device=dev)
+        x_t = room[1000:].view(n, n, n).copy_(x_t)
+        out = room[:n ** 3].view(n, n, n)
+    b = gpu.trace_step_noalloc(desc, nh_t, x_t, pos, ndot, out, cap)
+    for k in ("segments", "rays", "splits", "rays_per_level"):
+        assert b[k] == b_ref[k], k
+    assert rel(out.cpu().numpy(), ref) <= (1e-10 if prec == 0 else 1e-4)
