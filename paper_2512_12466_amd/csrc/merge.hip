@@ -23,6 +23,7 @@
 
 #include "healpix.h"
 #include "internal.h"
+#include "plan.h"
 
 namespace nrt {
 namespace {
@@ -644,15 +645,12 @@ hipError_t run_merge(nrt_ctx* c, const nrt_merge_params& mp, const double* h_ndo
   // general scratch: shell directions, scan temporaries, bins
   const int nsamp = 12 << (2 * mp.shell_level);
   const double reach = 2.0 * mp.f_ov * mp.r_max + std::sqrt(std::max(mp.eps, 0.0)) + 1.0;
-  int64_t nb = int64_t(std::floor(double(n) / reach));
-  if (nb < 3) nb = 1;
   auto scratch_need = [&](int64_t nbins) {
     const int64_t big = std::max(m, nbins);
     return align256z(size_t(nsamp) * 24) + align256z((size_t(big) / 1024 + 16) * 12) +
            3 * align256z(size_t(nbins) * 4);
   };
-  while (nb > 1 && scratch_need(nb * nb * nb) > c->scratch_bytes) --nb;
-  if (nb < 3) nb = 1;
+  const int64_t nb = merge_bins(n, reach, c->scratch_bytes, scratch_need);
   if (scratch_need(nb * nb * nb) > c->scratch_bytes) {
     why = "merge scratch exceeds the workspace scratch";
     return hipErrorInvalidValue;
