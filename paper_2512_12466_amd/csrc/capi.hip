@@ -10,6 +10,7 @@
 
 #include "healpix.h"
 #include "internal.h"
+#include "plan.h"
 
 using nrt::Accum;
 using nrt::Layout;
@@ -617,20 +618,6 @@ uint32_t line_multiplier(int n, int log2_lines) {
     }
   }
   return mul;
-}
-
-// Omega(l) = 4 pi / (12 4^l) (Eq. split_criterion), Omega_c = 1 / s^2: a ray
-// splits iff s*s > 1 / (N_min Omega(l)).  The rounded square is monotone in
-// s, so the test is a comparison with the smallest s that passes it, found
-// here a few steps from the square root.
-double split_length(double n_min_ray, int level) {
-  if (!(n_min_ray > 0.0)) return INFINITY;
-  const double omega = (4.0 * M_PI) / (12.0 * std::ldexp(1.0, 2 * level));
-  const double r2 = 1.0 / (n_min_ray * omega);
-  double s = std::sqrt(r2);
-  while (s > 0.0 && s * s > r2) s = std::nextafter(s, 0.0);
-  while (!(s * s > r2) && s < INFINITY) s = std::nextafter(s, INFINITY);
-  return s;
 }
 
 MarchArgs march_grid_args(const nrt_grid_desc& d, const double* a64,

@@ -154,10 +154,6 @@ MarchArgs march_grid_args(const nrt_grid_desc& d, const double* a64,
 // multiplier of the deposit table's slot hash for an n^3 grid and 2^log2_lines slots
 uint32_t line_multiplier(int n, int log2_lines);
 
-// smallest path length at which a ray of a level splits (Eq. split_criterion):
-// the smallest double s with s*s > 1 / (N_min Omega(level))
-double split_length(double n_min_ray, int level);
-
 // the reason a grid descriptor is invalid, or NULL (capi.hip)
 const char* check_grid_desc(const nrt_grid_desc* d);
 // set the message nrt_last_error(NULL) returns (fixed storage, no allocation)

@@ -15,6 +15,7 @@
 #include <mutex>
 
 #include "internal.h"
+#include "plan.h"
 
 // the pass's device state (absorber, sources, accumulators, level queues)
 static __device__ __align__(256) unsigned char scratch[size_t(64) << 20];

@@ -6,8 +6,32 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <cstring>
 
 namespace nrt {
+
+// The smallest path length at which a ray of a level splits (Eq.
+// split_criterion): Omega(l) = 4 pi / (12 4^l) and Omega_c = 1 / s^2, so a ray
+// splits iff s*s > 1 / (N_min Omega(l)).  The rounded square is monotone in s,
+// so the test is a comparison with the smallest s that passes it, found by
+// bisection over the ordered bit patterns of the doubles from 0 to infinity
+// (N_min Omega may overflow, which leaves s*s > 0, or its reciprocal may).
+// Infinity if none passes.
+inline double split_length(double n_min_ray, int level) {
+  if (!(n_min_ray > 0.0)) return INFINITY;
+  const double omega = (4.0 * M_PI) / (12.0 * std::ldexp(1.0, 2 * level));
+  const double r2 = 1.0 / (n_min_ray * omega);
+  uint64_t lo = 0, hi = uint64_t(0x7ff) << 52;  // 0 does not pass; infinity is the answer else
+  while (hi - lo > 1) {
+    const uint64_t mid = lo + (hi - lo) / 2;
+    double s;
+    std::memcpy(&s, &mid, sizeof(s));
+    (s * s > r2 ? hi : lo) = mid;
+  }
+  double s;
+  std::memcpy(&s, &hi, sizeof(s));
+  return s;
+}
 
 // Bins per axis of the merge's overlap search in an n^3 box: none narrower than
 // `reach` cells, the largest distance at which two bubbles overlap; 1 means no

@@ -36,10 +36,30 @@ static int merge_bins() {
   return 0;
 }
 
+// the smallest s whose rounded square passes the split test, over the accepted
+// N_min (finite, >= 0)
+static int split_length() {
+  const double n_mins[] = {0.0,    5e-324, 1e-310, 1e-308, 1e-300, 1e-20, 0.05, 1.0, 2.0,
+                           3.0,    4.0,    5.5,    64.0,   1e20,   1e300, 1e308, 1.71e308,
+                           1.717e308, 1.75e308, 1.7976931348623157e308};
+  for (double n_min : n_mins)
+    for (int level = 0; level <= 14; ++level) {
+      const double s = nrt::split_length(n_min, level);
+      const double omega = (4.0 * M_PI) / (12.0 * std::ldexp(1.0, 2 * level));
+      const double r2 = n_min > 0.0 ? 1.0 / (n_min * omega) : INFINITY;
+      CHECK(s > 0.0 && (s == INFINITY) == (r2 == INFINITY));
+      CHECK(s * s > r2 || s == INFINITY);
+      const double below = std::nextafter(s, 0.0);
+      CHECK(!(below * below > r2));
+    }
+  return 0;
+}
+
 int main(int argc, char** argv) {
   for (int a = 1; a < argc; ++a) {
     int bad = 1;
     if (!std::strcmp(argv[a], "merge_bins")) bad = merge_bins();
+    if (!std::strcmp(argv[a], "split_length")) bad = split_length();
     if (bad) {
       std::printf("%s failed\n", argv[a]);
       return 1;
