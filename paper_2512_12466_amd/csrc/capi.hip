@@ -400,53 +400,44 @@ void over_threads(int64_t count, int64_t least, Fn fn) {
 // 4^top / 2 azimuths (one for 32 pixels), so the host evaluates those and the
 // device forms the vectors from them by the same IEEE operations (128^3,
 // levels 0..9: 2 ms, where the host took 30 for the vectors and their copy).
-// Workspaces whose scratch does not hold the azimuths (levels past 9 on grids
-// below 128^3) take the vectors from the host.
+// Azimuths that do not fit the scratch space (levels past 9 on grids below
+// 128^3) go through it in windows, each launch writing the vectors of its
+// window (levels 0..10 at 32^3: 2.0 ms, 0..11 at 64^3: 8.7 ms; vectors formed on
+// the host took 112 and 418).
 nrt_status fill_direction_table(nrt_ctx* c) {
   const int top = c->lay.dir_levels;
   const int64_t azimuths = nrt::hp_azimuth_count(top);
-  const bool on_device = size_t(azimuths) * 16 <= c->scratch_bytes;
-  const int64_t total = nrt::dir_table_offset(top + 1);
+  const int64_t window = int64_t(c->scratch_bytes / 16);
   std::vector<double> tab;
   try {
-    tab.resize(on_device ? size_t(azimuths) * 2 : size_t(total) * 3);
-    if (on_device) {
-      over_threads(azimuths, 8192, [&](int64_t lo, int64_t hi) {
-        // ring of entry lo: the largest nr with (nr - 1)(nr - 2) / 2 <= lo
-        int nr = int(1.5 + std::sqrt(2.0 * double(lo) + 0.25));
-        while (nrt::hp_azimuth_index(nr, 1) > lo) --nr;
-        while (nrt::hp_azimuth_index(nr + 1, 1) <= lo) ++nr;
-        int k = int(lo - nrt::hp_azimuth_index(nr, 1)) + 1;
-        for (int64_t q = lo; q < hi; ++q) {
-          ::sincos(nrt::hp_azimuth(nr, k), &tab[size_t(2 * q + 1)], &tab[size_t(2 * q)]);
-          if (++k >= nr) {
-            ++nr;
-            k = 1;
-          }
+    tab.resize(size_t(azimuths) * 2);
+    over_threads(azimuths, 8192, [&](int64_t lo, int64_t hi) {
+      // ring of entry lo: the largest nr with (nr - 1)(nr - 2) / 2 <= lo
+      int nr = int(1.5 + std::sqrt(2.0 * double(lo) + 0.25));
+      while (nrt::hp_azimuth_index(nr, 1) > lo) --nr;
+      while (nrt::hp_azimuth_index(nr + 1, 1) <= lo) ++nr;
+      int k = int(lo - nrt::hp_azimuth_index(nr, 1)) + 1;
+      for (int64_t q = lo; q < hi; ++q) {
+        ::sincos(nrt::hp_azimuth(nr, k), &tab[size_t(2 * q + 1)], &tab[size_t(2 * q)]);
+        if (++k >= nr) {
+          ++nr;
+          k = 1;
         }
-      });
-    } else {
-      for (int l = 0; l <= top; ++l) {
-        const int64_t first = nrt::dir_table_offset(l);
-        over_threads(12 * (int64_t(1) << (2 * l)), 4096, [&](int64_t lo, int64_t hi) {
-          for (int64_t p = lo; p < hi; ++p) {
-            double* d = tab.data() + 3 * (first + p);
-            const nrt::HpAngle a = nrt::healpix_angle(l, uint32_t(p));
-            double ca = 1.0, sa = 0.0;
-            if (a.fold >= 2) ::sincos(a.ang, &sa, &ca);
-            nrt::healpix_vector(a, ca, sa, d[0], d[1], d[2]);
-          }
-        });
       }
-    }
+    });
   } catch (const std::bad_alloc&) {
     return fail(c, NRT_ERR_NOMEM, "host memory for the direction table");
   }
-  double* to = on_device ? reinterpret_cast<double*>(c->scratch) : c->dirs;
-  if (!tab.empty())
-    HIP_OR_FAIL(c, hipMemcpyAsync(to, tab.data(), tab.size() * sizeof(double),
-                                  hipMemcpyHostToDevice, c->stream));
-  if (on_device) HIP_OR_FAIL(c, nrt::launch_directions(top, to, c->dirs, c->stream));
+  double* cs = reinterpret_cast<double*>(c->scratch);
+  int64_t lo = 0;
+  do {  // once even without azimuths: level 0 has none
+    const int64_t hi = std::min(azimuths, lo + window);
+    if (hi > lo)
+      HIP_OR_FAIL(c, hipMemcpyAsync(cs, tab.data() + 2 * lo, size_t(hi - lo) * 16,
+                                    hipMemcpyHostToDevice, c->stream));
+    HIP_OR_FAIL(c, nrt::launch_directions(top, lo, hi, cs, c->dirs, c->stream));
+    lo = hi;
+  } while (lo < azimuths);
   HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
   return NRT_OK;
 }

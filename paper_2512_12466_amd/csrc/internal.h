@@ -248,9 +248,11 @@ hipError_t launch_rt_reset(RtState* rt, hipStream_t s);
 hipError_t launch_march(const nrt_ctx* c, const MarchArgs& a, int64_t rays, hipStream_t st);
 hipError_t march_blocks_per_cu(const nrt_grid_desc& d, int* blocks);
 hipError_t launch_healpix(int level, int64_t first, int64_t count, double* out, hipStream_t s);
-// the direction table of levels 0..levels from the cosine and sine of its
-// azimuths (hp_azimuth_index)
-hipError_t launch_directions(int levels, const double* cos_sin, double* out, hipStream_t s);
+// the direction table's pixels with azimuths lo..hi-1 (hp_azimuth_index), of
+// levels 0..levels, from their cosines and sines; with lo = 0 also those that
+// need no azimuth
+hipError_t launch_directions(int levels, int64_t lo, int64_t hi, const double* cos_sin,
+                             double* out, hipStream_t s);
 // the threshold optical depth where a spectrum's Phi reaches tau_max, written
 // to one device double (the spectrum table must be built)
 hipError_t launch_spec_stop(const nrt_ctx* c, double* out);

@@ -1062,15 +1062,24 @@ __global__ void k_healpix(int level, int64_t first, int64_t count, double* out) 
 
 // Entry q of the direction table: levels 0..top in turn, each pixel's vector
 // from the geometry (IEEE operations, so the host's values) and the host's
-// cosine and sine of its azimuth.
-__global__ void k_directions(int64_t total, const double2* __restrict__ cs, double* out) {
+// cosine and sine of its azimuth.  A launch holds the azimuths [lo, hi) in cs
+// and writes their pixels; the pixels without an azimuth of their own go with
+// the first launch.
+__global__ void k_directions(int64_t total, int64_t lo, int64_t hi,
+                             const double2* __restrict__ cs, double* out) {
   const int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (q >= total) return;
   // a level's entries start at 4 (4^level - 1)
   const int level = (31 - __clz(uint32_t(q / 4 + 1))) / 2;
   const HpAngle a = healpix_angle(level, uint32_t(q - dir_table_offset(level)));
   double2 t{1.0, 0.0};
-  if (a.fold >= 2) t = cs[hp_azimuth_index(a.nr, a.k)];
+  if (a.fold >= 2) {
+    const int64_t i = hp_azimuth_index(a.nr, a.k);
+    if (i < lo || i >= hi) return;
+    t = cs[i - lo];
+  } else if (lo > 0) {
+    return;
+  }
   healpix_vector(a, t.x, t.y, out[3 * q], out[3 * q + 1], out[3 * q + 2]);
 }
 
@@ -1278,10 +1287,11 @@ hipError_t launch_budget(const Accum* acc, nrt_budget* out, uint64_t* dropped, d
   return hipGetLastError();
 }
 
-hipError_t launch_directions(int levels, const double* cos_sin, double* out, hipStream_t s) {
+hipError_t launch_directions(int levels, int64_t lo, int64_t hi, const double* cos_sin,
+                             double* out, hipStream_t s) {
   const int64_t total = dir_table_offset(levels + 1);
-  hipLaunchKernelGGL(k_directions, dim3(unsigned((total + 255) / 256)), dim3(256), 0, s, total,
-                     reinterpret_cast<const double2*>(cos_sin), out);
+  hipLaunchKernelGGL(k_directions, dim3(unsigned((total + 255) / 256)), dim3(256), 0, s, total, lo,
+                     hi, reinterpret_cast<const double2*>(cos_sin), out);
   return hipGetLastError();
 }
 

@@ -65,3 +65,54 @@ def test_direction_table_levels(gpu, orc, n, l_max):
             np.testing.assert_array_equal(ctx.healpix_dirs(level, first, count), ref,
                                           err_msg=str((level, first)))
     ctx.destroy()
+
+
+def test_direction_table_windows(gpu, orc):
+    """Levels to 11 on a 4^3 grid: the azimuths pass through the scratch space
+    (2^18 of them at a time) in eight windows.  The pixels on both sides of
+    every window's ends, from the oracle; and the table takes the device's
+    time, not the host's, which is hundreds of times level 9's (16 times the
+    pixels and 8 passes over them: bounded by 60 times)."""
+    import time
+
+    import torch
+    one = torch.ones((4, 4, 4), dtype=torch.float64, device="cuda:0")
+
+    def init(l_max):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        ctx = gpu.init_grid(gpu.make_desc(4, 1e20, l_max=l_max), one, 0 * one, device="cuda:0",
+                            max_sources=1, ray_capacity=4096)
+        torch.cuda.synchronize()
+        return ctx, time.perf_counter() - t0
+
+    level, ns = 11, 1 << 11
+    ctx, _ = init(level)
+    # azimuth index -> ring nr and step k of the north cap, whose pixels lie at
+    # the odd steps: one of each pair of neighbours is a pixel's
+    for edge in [w << 18 for w in range(1, 8)]:
+        for i in (edge - 1, edge):
+            nr = int(1.5 + np.sqrt(2.0 * i + 0.25))
+            while (nr - 1) * (nr - 2) // 2 > i:
+                nr -= 1
+            k = i - (nr - 1) * (nr - 2) // 2 + 1
+            # face 0 (jpll 1): num = nr + ix - iy = k, ring 2 ns - ix - iy - 1 = nr
+            if k % 2 == 0:
+                continue
+            d, t = k - nr, 2 * ns - 1 - nr
+            ix, iy = (t + d) // 2, (t - d) // 2
+            pix = sum(((ix >> b) & 1) << (2 * b) | ((iy >> b) & 1) << (2 * b + 1)
+                      for b in range(11))
+            np.testing.assert_array_equal(ctx.healpix_dirs(level, pix, 1)[0],
+                                          orc.pix2vec_nest(level, pix), err_msg=str((nr, k)))
+    g = np.random.default_rng(3)
+    for pix in g.integers(0, 12 * 4 ** level, 300).tolist():
+        np.testing.assert_array_equal(ctx.healpix_dirs(level, pix, 1)[0],
+                                      orc.pix2vec_nest(level, pix), err_msg=str(pix))
+    ctx.destroy()
+    times = {}
+    for l_max in (9, 11, 9, 11):
+        ctx, t = init(l_max)
+        ctx.destroy()
+        times[l_max] = min(t, times.get(l_max, np.inf))
+    assert times[11] < 60 * times[9], times
