@@ -113,13 +113,24 @@ struct LaneAcc {
 // lanes one by one).  So a deposit reads its slot's key and swaps only where
 // its line is new, instead of a swap by every lane, and deposits are summed
 // in FP64 (see march_kernel for the exception).  A deposit that finds no slot
-// within kProbe probes goes straight to Gamma.
+// within kProbe probes goes straight to Gamma, and on grids whose lines do not
+// fit the 32-bit keys (n >= 3251; the 64-bit cell index only) all of them do.
 constexpr int kWaves = kBlock / 64;
 constexpr int kLine = 8;
 constexpr int kProbe = 16;
 constexpr uint32_t kEmpty = 0xffffffffu;
 
-template <typename V>
+// Sizes at which the march's cell index and table change.  A second build of
+// the library, for the tests, sets them so that small grids take the 64-bit
+// index and both sides of the table's limit.
+#ifndef NRT_NARROW_CELLS
+#define NRT_NARROW_CELLS (int64_t(1) << 32)  // most cells of the 32-bit index
+#endif
+#ifndef NRT_TABLE_LINES
+#define NRT_TABLE_LINES int64_t(kEmpty)  // lines below this many have a key
+#endif
+
+template <typename V, typename Idx>
 struct LineTable {
   // line slots per wavefront: 37 KiB (FP32 sums) or 34.5 KiB (FP64) per block
   static constexpr int kLog2Lines = sizeof(V) == 4 ? kLog2LinesFp32 : kLog2LinesFp64;
@@ -131,18 +142,19 @@ struct LineTable {
   static constexpr size_t kWaveBytes =
       kLines * (sizeof(uint32_t) + sizeof(uint8_t) + kLine * sizeof(V));
 
-  uint32_t* key;  // [kLines] line index (cell >> 3, below 2^32 - 1 on any grid that fits the
-                  // device's memory) or kEmpty
+  uint32_t* key;  // [kLines] line index (cell >> 3) or kEmpty
   V* val;         // [kLines * kLine] partial sums of the line's cells
   uint8_t* list;  // [kLines] slots in use, compacted by a flush
   uint32_t mul;   // multiplier of the slot hash (line_multiplier)
+  bool keys_fit;  // of a grid with the 64-bit index
+
+  __device__ __forceinline__ bool staged() const { return sizeof(Idx) == 4 || keys_fit; }
 
   // First slot of the line of cell c and the key it holds, read ahead of the
   // arithmetic that precedes the deposit.
   struct Look {
     uint32_t k, h, old;
   };
-  template <typename Idx>
   __device__ __forceinline__ Look look(Idx c) const {
     Look l;
     l.k = uint32_t(c >> 3);
@@ -157,7 +169,7 @@ struct LineTable {
   // claim); counts a new line in `inserted`.  After it, l.old == l.k tells
   // that the slot is the line's.
   __device__ __forceinline__ void claim(Look& l, bool claim, int& inserted) const {
-    if (claim && l.old != l.k) {
+    if (claim && l.old != l.k && staged()) {
       l.old = atomicCAS(&key[l.h], kEmpty, l.k);
       if (l.old == kEmpty) {
         l.old = l.k;
@@ -168,9 +180,12 @@ struct LineTable {
 
   // add v for cell c (lanes with want) to the line's slot, probing further
   // (lanes with claim) if its first slot belongs to another line
-  template <typename Idx>
   __device__ __forceinline__ void deposit(Look& l, Idx c, V v, bool claim, bool want,
                                           int& inserted) const {
+    if (!staged()) {
+      if (want) atomicAdd(fresh_args().gamma + c, double(v));
+      return;
+    }
     const uint32_t sub = uint32_t(c) & uint32_t(kLine - 1);
     if (claim && l.old != l.k) {
 #pragma unroll 1
@@ -552,7 +567,7 @@ __device__ __forceinline__ int stop_code(const Args& A, const RayState<Idx>& R) 
 // and the neighbour's load, and the deposits come last.
 template <bool MIXED, int CORR, bool PERIODIC, bool POLY, typename V, typename Idx>
 __device__ __forceinline__ int ray_step(RayState<Idx>& R, const MarchArgs& A,
-                                        const LineTable<V>& tab, LaneAcc& acc, int& inserted,
+                                        const LineTable<V, Idx>& tab, LaneAcc& acc, int& inserted,
                                         const StepConst& K) {
   constexpr bool neighbours = CORR == NRT_CORR_CONSERVATIVE || CORR == NRT_CORR_NAIVE;
   if (R.s >= K.s_stop || R.tau >= K.tau_stop) return stop_code<PERIODIC>(fresh_args(), R);
@@ -833,7 +848,7 @@ __attribute__((amdgpu_waves_per_eu((MIXED || PERIODIC || !POLY) ? 4 : 3, 8))) vo
   const int64_t first_runs = nwaves * run;
   if (int64_t(blockIdx.x) * kWaves * run >= total) return;
   // per-wavefront deposit tables, reused for the budget reduction at the end
-  using Tab = LineTable<V>;
+  using Tab = LineTable<V, Idx>;
   __shared__ __align__(16) unsigned char lds[kWaves * Tab::kWaveBytes];
   const int wave = threadIdx.x >> 6;
   const int lane = __lane_id();
@@ -844,7 +859,7 @@ __attribute__((amdgpu_waves_per_eu((MIXED || PERIODIC || !POLY) ? 4 : 3, 8))) vo
                   wave * Tab::kLines;
   uint32_t mul = sizeof(V) == 4 ? A.line_mul[0] : A.line_mul[1];
   asm volatile("" : "+s"(mul));
-  const Tab tab{key, val, list, mul};
+  const Tab tab{key, val, list, mul, (int64_t(A.n) * A.n * A.n) >> 3 < NRT_TABLE_LINES};
   for (int q = lane; q < Tab::kLines; q += 64) key[q] = kEmpty;
   for (int q = lane; q < Tab::kLines * kLine; q += 64) val[q] = V(0);
   __builtin_amdgcn_wave_barrier();
@@ -1219,7 +1234,7 @@ bool wide_sums(const nrt_grid_desc& d, int level) {
 }
 
 MarchKernel march_kernel(const nrt_grid_desc& d, int level) {
-  const bool wide = int64_t(d.n) * d.n * d.n > (int64_t(1) << 32);
+  const bool wide = int64_t(d.n) * d.n * d.n > NRT_NARROW_CELLS;
   if (d.precision != NRT_MIXED)
     return wide ? march_for<false, double, int64_t>(d) : march_for<false, double, uint32_t>(d);
   if (!wide_sums(d, level))
