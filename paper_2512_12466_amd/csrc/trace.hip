@@ -803,14 +803,22 @@ __device__ __forceinline__ void push_pending(unsigned long long* count, const Ra
 // cells a ray: runs of 64 / 128 / 256 take 8.5 / 7.1 / 6.6 ms); long runs
 // leave a long tail where rays are long (1024^3, 100 cells a ray: 221 / 234 /
 // 262 ms).  So the run follows the cells that 64 rays of the last one took,
-// within the wavefront's even share of what is left.
-__device__ __forceinline__ int64_t run_size(int64_t cells_per_64, int64_t left, float share,
-                                            int64_t lo, int64_t hi) {
+// within the wavefront's even share of what is left.  The share is rounded down
+// to whole wavefronts, but up in launches of brief rays (kBriefStop), whose
+// second 64 take less time than one more claim by every wavefront (128^3, FP64,
+// 1.7 / 3 / 10 cells a ray: 113 / 610 / 2334 us rounded down, 84 / 532 / 1793
+// up; where rays are longer, rounding up costs: 1024^3 +2 %).
+__device__ __forceinline__ int64_t run_size(int64_t cells_per_64, bool brief, int64_t left,
+                                            float share, int64_t lo, int64_t hi) {
   const int64_t by_cells = cells_per_64 <= 16 ? 256 : (cells_per_64 <= 32 ? 128 : 64);
-  const int64_t even = int64_t(float(left) * share) & ~int64_t(63);
+  const int64_t even = int64_t(float(left) * share + (brief ? 63.99f : 0.0f)) & ~int64_t(63);
   const int64_t r = by_cells < even ? by_cells : even;
   return r < lo ? lo : (r > hi ? hi : r);
 }
+
+// Bound on the path length of a launch whose rays are brief, 16 cells or fewer: a
+// level's rays start at half of it, and take 1.5 cells a unit of length.
+constexpr double kBriefStop = 21.0;
 
 // Persistent march: every wavefront takes runs of rays of the launch's range
 // (its first by position, the rest from a shared counter; their size from
@@ -844,7 +852,9 @@ __attribute__((amdgpu_waves_per_eu((MIXED || PERIODIC || !POLY) ? 4 : 3, 8))) vo
   // issues no atomics.
   const int64_t nwaves = int64_t(gridDim.x) * kWaves;
   const float share = 1.0f / float(nwaves);
-  int64_t run = run_size(0, total, 0.25f * share, A.claim_min, A.claim);
+  // brief rays: the even share, so that often no run is left to claim
+  const bool brief = A.s_stop <= kBriefStop;
+  int64_t run = run_size(0, brief, total, brief ? share : 0.25f * share, A.claim_min, A.claim);
   const int64_t first_runs = nwaves * run;
   if (int64_t(blockIdx.x) * kWaves * run >= total) return;
   // per-wavefront deposit tables, reused for the budget reduction at the end
@@ -886,10 +896,12 @@ __attribute__((amdgpu_waves_per_eu((MIXED || PERIODIC || !POLY) ? 4 : 3, 8))) vo
     const int n_idle = __popcll(idle);
     if (!exhausted && (n_idle >= A.refill_min || n_idle == 64)) {
       ArgsK& F = fresh_args();
-      if (pool == pool_end) {
+      if (pool == pool_end && first_runs >= total) {
+        exhausted = true;  // the first runs were all: no claim is needed to tell
+      } else if (pool == pool_end) {
         // what is left by this wavefront's last run (others may have taken more)
         const int64_t left = total - (pool > first_runs ? pool : first_runs);
-        run = run_size(int64_t(iterations) * kCellsPerIteration * 64 / run, left, share,
+        run = run_size(int64_t(iterations) * kCellsPerIteration * 64 / run, brief, left, share,
                        F.claim_min, F.claim);
         iterations = 0;
         unsigned long long b = 0;
@@ -983,12 +995,13 @@ __attribute__((amdgpu_waves_per_eu((MIXED || PERIODIC || !POLY) ? 4 : 3, 8))) vo
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0 && (red_u[0] != 0 || red_d[1][0] != 0.0 || red_d[2][0] != 0.0)) {
-    // a block that marched nothing and stopped no ray adds nothing
-    atomicAdd(&A.acc->absorbed, red_d[0][0]);
-    atomicAdd(&A.acc->escaped, red_d[1][0]);
-    atomicAdd(&A.acc->truncated, red_d[2][0]);
-    atomicAdd(&A.acc->segments, red_u[0]);
+  // a term that is zero adds nothing: these are same-address atomics too, 8 us
+  // a term and launch (l_max 4 at 128^3: 648 -> 630 us)
+  if (threadIdx.x == 0) {
+    if (red_d[0][0] != 0.0) atomicAdd(&A.acc->absorbed, red_d[0][0]);
+    if (red_d[1][0] != 0.0) atomicAdd(&A.acc->escaped, red_d[1][0]);
+    if (red_d[2][0] != 0.0) atomicAdd(&A.acc->truncated, red_d[2][0]);
+    if (red_u[0] != 0) atomicAdd(&A.acc->segments, red_u[0]);
   }
 }
 

@@ -116,3 +116,34 @@ def test_direction_table_windows(gpu, orc):
         ctx.destroy()
         times[l_max] = min(t, times.get(l_max, np.inf))
     assert times[11] < 60 * times[9], times
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("m", [5, 2731, 21845, 21846, 43690, 43691, 65536, 65537, 87381, 87382])
+def test_first_runs(gpu, m, prec):
+    """Launches whose rays the first runs just cover or just do not (12 m rays
+    at level 0: 64, 128, 192 and 256 for each of 4096 wavefronts): every ray is
+    marched once whatever the run sizes, so the counts agree with fixed runs of
+    128, and each term of the budget to the rounding of its sums."""
+    n = 32
+    g = np.random.default_rng(m)
+    x = np.where(g.random((n, n, n)) < 0.3, 1.0 - 1e-4, 0.0)
+    nH = 1e-3 * np.exp(g.standard_normal((n, n, n)))
+    pos = W.uniform_positions(m, n, g)
+    ndot = W.lognormal_values(m, 1e50, 1.0, g)
+    h = 2.0 / (W.SIGMA0 * 1e-3)  # rays stop in both ways
+    ctx = gpu.init_grid(gpu.make_desc(n, h, periodic=False, n_min_ray=4.0, l_max=1,
+                                      precision=prec), nH, x, device="cuda:0", max_sources=m,
+                        ray_capacity=1 << 22)
+    ctx.add_sources(pos, ndot)
+    ctx.set_tuning(refill_min=16, claim=128, graph=1)
+    _, ref = ctx.trace_step()
+    assert ref["rays_per_level"][0] == 12 * m and ref["truncated"] > 0 and ref["escaped"] > 0
+    for graph in (1, 2):
+        ctx.set_tuning(graph=graph)
+        _, b = ctx.trace_step()
+        assert [b[k] for k in ("segments", "rays", "splits", "rays_per_level")] == [
+            ref[k] for k in ("segments", "rays", "splits", "rays_per_level")]
+        for k in ("absorbed", "escaped", "truncated"):
+            assert abs(b[k] - ref[k]) <= (1e-10 if prec == 0 else 1e-6) * ref["emitted"], k
+    ctx.destroy()
