@@ -1118,16 +1118,11 @@ nrt_status nrt_autotune(nrt_ctx* c, double* gamma_scratch, int32_t passes, nrt_t
   if (!c) return fail(nullptr, NRT_ERR_ARG, "ctx is NULL");
   if (!gamma_scratch || !best || passes < 1) return fail(c, NRT_ERR_ARG, "bad autotune arguments");
   const nrt_tuning keep = c->tuning;
-  std::vector<nrt_tuning> cand;
-  const int max_bpc = std::max(1, c->march_blocks_per_cu);
-  // refill 64: a wavefront refills only once drained (the best choice where
-  // the rays of a run live equally long)
-  for (int refill : {8, 16, 32, 64})
-    for (int claim : {0, 64, 256})
-      for (int bpc : {0, std::max(1, max_bpc - 1)}) {
-        if (bpc != 0 && bpc == max_bpc) continue;
-        cand.push_back(nrt_tuning{refill, claim, bpc, keep.graph});
-      }
+  const std::vector<nrt_tuning> cand = nrt::tuning_candidates(keep, c->march_blocks_per_cu);
+  // an untimed pass first: the first candidate would else be timed while the
+  // kernels load, and host-driven where the others replay a graph
+  nrt_budget warm;
+  if (const nrt_status st = trace_pass(c, gamma_scratch, &warm)) return st;
   double best_ms = INFINITY;
   nrt_tuning win = keep;
   for (const nrt_tuning& t : cand) {

@@ -7,8 +7,32 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <vector>
+
+#include "nyxrt.h"
 
 namespace nrt {
+
+// Launch parameters that the autotuner times, in order: the library's default,
+// the ones in use (`now`), and a grid around them.  The first two are there
+// because the default differs by level (zeros), which no fixed choice can say.
+// Refill 64: a wavefront refills only once drained (the best where the rays of
+// a run live equally long).
+inline std::vector<nrt_tuning> tuning_candidates(const nrt_tuning& now, int max_blocks_per_cu) {
+  std::vector<nrt_tuning> cand{nrt_tuning{0, 0, 0, now.graph}};
+  auto add = [&](const nrt_tuning& t) {
+    for (const nrt_tuning& c : cand)
+      if (std::memcmp(&c, &t, sizeof(t)) == 0) return;
+    cand.push_back(t);
+  };
+  add(now);
+  const int most = std::max(1, max_blocks_per_cu);
+  for (int refill : {8, 16, 32, 64})
+    for (int claim : {0, 64, 256})
+      for (int bpc : {0, std::max(1, most - 1)})
+        if (bpc != most) add(nrt_tuning{refill, claim, bpc, now.graph});
+  return cand;
+}
 
 // The smallest path length at which a ray of a level splits (Eq.
 // split_criterion): Omega(l) = 4 pi / (12 4^l) and Omega_c = 1 / s^2, so a ray

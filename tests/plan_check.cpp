@@ -55,11 +55,35 @@ static int split_length() {
   return 0;
 }
 
+// the default and the set in use are among the autotuner's candidates, each
+// candidate once and within what nrt_set_tuning takes
+static int tuning_candidates() {
+  const nrt_tuning sets[] = {{0, 0, 0, 0}, {16, 128, 0, 2}, {64, 64, 3, 1}, {5, 65536, 2, 0}};
+  for (const nrt_tuning& now : sets)
+    for (int most : {0, 1, 3, 4}) {
+      const auto cand = nrt::tuning_candidates(now, most);
+      int dflt = 0, in_use = 0;
+      for (size_t i = 0; i < cand.size(); ++i) {
+        const nrt_tuning& t = cand[i];
+        dflt += t.refill_min == 0 && t.claim == 0 && t.blocks_per_cu == 0;
+        in_use += std::memcmp(&t, &now, sizeof(t)) == 0;
+        CHECK(t.refill_min >= 0 && t.refill_min <= 64 && t.claim >= 0 && t.claim <= 65536 &&
+              t.claim % 64 == 0 && t.blocks_per_cu >= 0 && t.blocks_per_cu <= 64);
+        CHECK(t.graph == now.graph);
+        for (size_t j = 0; j < i; ++j) CHECK(std::memcmp(&t, &cand[j], sizeof(t)) != 0);
+      }
+      CHECK(dflt == 1 && in_use == 1);
+      CHECK(cand.size() >= 12);
+    }
+  return 0;
+}
+
 int main(int argc, char** argv) {
   for (int a = 1; a < argc; ++a) {
     int bad = 1;
     if (!std::strcmp(argv[a], "merge_bins")) bad = merge_bins();
     if (!std::strcmp(argv[a], "split_length")) bad = split_length();
+    if (!std::strcmp(argv[a], "tuning_candidates")) bad = tuning_candidates();
     if (bad) {
       std::printf("%s failed\n", argv[a]);
       return 1;

@@ -20,7 +20,7 @@ def check(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("name", ["merge_bins", "split_length"])
+@pytest.mark.parametrize("name", ["merge_bins", "split_length", "tuning_candidates"])
 def test_plan(check, name):
     p = subprocess.run([check, name], capture_output=True, text=True, timeout=60)
     assert p.returncode == 0, p.stdout + p.stderr
