@@ -10,7 +10,6 @@
 
 #include "healpix.h"
 #include "internal.h"
-#include "plan.h"
 
 using nrt::Accum;
 using nrt::Layout;
@@ -78,8 +77,6 @@ const char* check_desc(const nrt_grid_desc* d) {
 void level_constants(nrt_ctx* c) {
   for (int l = 0; l <= nrt::kMaxLevel; ++l)
     c->s_split[l] = nrt::split_length(c->desc.n_min_ray, l);
-  c->line_mul[0] = nrt::line_multiplier(c->desc.n, nrt::kLog2LinesFp32);
-  c->line_mul[1] = nrt::line_multiplier(c->desc.n, nrt::kLog2LinesFp64);
 }
 
 nrt_status sync_read_accum(nrt_ctx* c) {
@@ -116,8 +113,6 @@ nrt_status upload_sources(nrt_ctx* c) {
 MarchArgs base_args(const nrt_ctx* c, double* gamma) {
   MarchArgs a = nrt::march_grid_args(c->desc, c->a64, gamma, c->acc);
   a.tau_stop = c->desc.spectrum != NRT_SPEC_MONO ? c->spec_tau_stop : c->desc.tau_max;
-  a.line_mul[0] = c->line_mul[0];
-  a.line_mul[1] = c->line_mul[1];
   a.src_pos = c->src_pos;
   a.src_l0 = c->src_l0;
   a.dirs = c->dirs;
@@ -571,46 +566,6 @@ const char* check_grid_desc(const nrt_grid_desc* d) { return check_desc(d); }
 
 void set_error(const char* msg) { set_init_error(msg); }
 
-// The slot of a line in a wavefront's deposit table is the top log2_lines bits
-// of (line * M mod 2^24).  A bundle of rays fills the lines of a few cells
-// around it, so M should send nearby lines (line +- 1 along x, n/8 along y,
-// n^2/8 along z) to different slots, which depends on n: of 64 multipliers,
-// the one with the least overlap of neighbours, weighted by a Gaussian of 4
-// cells.  An emulation of bundles on nine grids of 64^3 to 1024^3, 128 slots
-// folded at a quarter: a step of the wavefront probes past a first slot
-// 0.3 times with it, 0.8 times with the golden-ratio multiplier.
-uint32_t line_multiplier(int n, int log2_lines) {
-  constexpr int kReach = 5;
-  const uint32_t slot = 0x1000000u >> log2_lines;
-  double weight[2 * kReach * kReach + 1];
-  for (int r = 0; r <= 2 * kReach * kReach; ++r) weight[r] = std::exp(-r / 32.0);
-  double best = INFINITY;
-  uint32_t mul = 0, x = 0x9E3779B9u;
-  for (int q = 0; q < 64; ++q) {
-    x = x * 1664525u + 1013904223u;
-    const uint32_t m = (x >> 8) | 1u;
-    double score = 0.0;
-    for (int dz = 0; dz <= kReach; ++dz)
-      for (int dy = dz ? -kReach : 0; dy <= kReach; ++dy) {
-        const int64_t cells = int64_t(n) * dy + int64_t(n) * n * dz;
-        // rows that do not start on a line share one with both neighbours
-        const bool aligned = cells % 8 == 0;
-        for (int dx = dz || dy ? -1 : 1; dx <= (aligned ? 1 : 2); ++dx) {
-          const uint32_t p = (uint32_t(cells >> 3) + uint32_t(dx)) * m & 0xffffffu;
-          const uint32_t gap = p >= 0x800000u ? 0x1000000u - p : p;
-          const int cx = 8 * dx - (aligned ? 0 : 4);
-          if (gap < slot)
-            score += double(slot - gap) * weight[dy * dy + dz * dz] * (cx == 0 ? 1.0 : std::exp(-cx * cx / 32.0));
-        }
-      }
-    if (score < best) {
-      best = score;
-      mul = m;
-    }
-  }
-  return mul;
-}
-
 MarchArgs march_grid_args(const nrt_grid_desc& d, const double* a64,
                           double* gamma, Accum* acc) {
   MarchArgs a;
@@ -630,6 +585,9 @@ MarchArgs march_grid_args(const nrt_grid_desc& d, const double* a64,
   a.kf = float(d.sigma0 * d.h_cm);
   a.a64 = a64;
   a.gamma = gamma;
+  const LineMultipliers mul = line_multipliers(d.n);
+  a.line_mul[0] = mul.fp32;
+  a.line_mul[1] = mul.fp64;
   a.dir_max_level = -1;  // no direction table: directions computed in the march
   for (int l = 0; l <= kMaxLevel; ++l) {
     const double omega = (4.0 * M_PI) / (12.0 * std::ldexp(1.0, 2 * l));

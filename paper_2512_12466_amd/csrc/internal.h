@@ -10,14 +10,12 @@
 #include <vector>
 
 #include "nyxrt.h"
+#include "plan.h"
 
 namespace nrt {
 
 constexpr int kMaxLevel = NRT_MAX_LEVEL;
 constexpr int kBlock = 256;  // threads per block of the march kernels (4 waves)
-
-// Line slots of a wavefront's deposit table (trace.hip), by the type of its sums.
-constexpr int kLog2LinesFp32 = 8, kLog2LinesFp64 = 7;
 
 // One ray in a level queue (structure of arrays, 24 bytes per ray).  The
 // HEALPix level is the queue's, the rate follows from the source and level,
@@ -151,9 +149,6 @@ Layout plan_layout(const nrt_grid_desc& d, int64_t max_sources, int64_t capacity
 MarchArgs march_grid_args(const nrt_grid_desc& d, const double* a64,
                           double* gamma, Accum* acc);
 
-// multiplier of the deposit table's slot hash for an n^3 grid and 2^log2_lines slots
-uint32_t line_multiplier(int n, int log2_lines);
-
 // the reason a grid descriptor is invalid, or NULL (capi.hip)
 const char* check_grid_desc(const nrt_grid_desc* d);
 // set the message nrt_last_error(NULL) returns (fixed storage, no allocation)
@@ -209,7 +204,6 @@ struct nrt_ctx {
   nrt::Accum* h_acc;
   // per-level constants (host-computed, FP64)
   double s_split[nrt::kMaxLevel + 1];
-  uint32_t line_mul[2];  // see MarchArgs
   // timing of the last pass
   std::vector<hipEvent_t> ev;
   int launches;

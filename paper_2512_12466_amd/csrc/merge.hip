@@ -23,7 +23,6 @@
 
 #include "healpix.h"
 #include "internal.h"
-#include "plan.h"
 
 namespace nrt {
 namespace {

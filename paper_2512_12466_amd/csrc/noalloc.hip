@@ -15,7 +15,6 @@
 #include <mutex>
 
 #include "internal.h"
-#include "plan.h"
 
 // the pass's device state (absorber, sources, accumulators, level queues)
 static __device__ __align__(256) unsigned char scratch[size_t(64) << 20];
@@ -159,20 +158,10 @@ nrt_status nrt_trace_step_noalloc(const nrt_grid_desc* desc, const double* n_H,
   // the device-driven pass: one launch per HEALPix level, each reading its
   // ray count from the count the previous level wrote
   const nrt_tuning t = {0, 0, 0, 0};
-  // the hash multipliers of the last grid size a thread called with
-  thread_local int mul_n = 0;
-  thread_local uint32_t mul[2];
-  if (mul_n != desc->n) {
-    mul[0] = nrt::line_multiplier(desc->n, nrt::kLog2LinesFp32);
-    mul[1] = nrt::line_multiplier(desc->n, nrt::kLog2LinesFp64);
-    mul_n = desc->n;
-  }
   for (int level = 0; level <= desc->l_max && m > 0; ++level) {
     nrt::MarchArgs a = nrt::march_grid_args(*desc, a64, gamma_out, acc);
     a.src_pos = src_pos;
     a.src_l0 = src_l0;
-    a.line_mul[0] = mul[0];
-    a.line_mul[1] = mul[1];
     a.level = level;
     a.spawn = level == 0 ? 1 : 0;
     a.begin = 0;

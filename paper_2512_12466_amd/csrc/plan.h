@@ -4,14 +4,80 @@
 #pragma once
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdint>
+#include <cstdlib>
 #include <cstring>
 #include <vector>
 
 #include "nyxrt.h"
 
 namespace nrt {
+
+// Line slots of a wavefront's deposit table (trace.hip), by the type of its sums.
+constexpr int kLog2LinesFp32 = 8, kLog2LinesFp64 = 7;
+
+// The slot of a line in a wavefront's deposit table is the top log2_lines bits
+// of (line * M mod 2^24).  A bundle of rays fills the lines of a few cells
+// around it, so M should send nearby lines (line +- 1 along x, n/8 along y,
+// n^2/8 along z) to different slots, which depends on n: of 64 multipliers,
+// the one with the least overlap of neighbours, weighted by a Gaussian of 4
+// cells.  An emulation of bundles on nine grids of 64^3 to 1024^3, 128 slots
+// folded at a quarter: a step of the wavefront probes past a first slot
+// 0.3 times with it, 0.8 times with the golden-ratio multiplier.
+inline uint32_t line_multiplier(int n, int log2_lines) {
+  constexpr int kReach = 5;
+  const uint32_t slot = 0x1000000u >> log2_lines;
+  double weight[2 * kReach * kReach + 1];
+  for (int r = 0; r <= 2 * kReach * kReach; ++r) weight[r] = std::exp(-r / 32.0);
+  // of |x| = 0, 4, 8, 12 cells
+  const double along[4] = {1.0, std::exp(-0.5), std::exp(-2.0), std::exp(-4.5)};
+  double best = INFINITY;
+  uint32_t mul = 0, x = 0x9E3779B9u;
+  for (int q = 0; q < 64; ++q) {
+    x = x * 1664525u + 1013904223u;
+    const uint32_t m = (x >> 8) | 1u;
+    double score = 0.0;  // only grows: a multiplier past the best so far is left
+    for (int dz = 0; dz <= kReach && score < best; ++dz)
+      for (int dy = dz ? -kReach : 0; dy <= kReach; ++dy) {
+        const int64_t cells = int64_t(n) * dy + int64_t(n) * n * dz;
+        // rows that do not start on a line share one with both neighbours
+        const bool aligned = cells % 8 == 0;
+        for (int dx = dz || dy ? -1 : 1; dx <= (aligned ? 1 : 2); ++dx) {
+          const uint32_t p = (uint32_t(cells >> 3) + uint32_t(dx)) * m & 0xffffffu;
+          const uint32_t gap = p >= 0x800000u ? 0x1000000u - p : p;
+          const int cx = 8 * dx - (aligned ? 0 : 4);
+          if (gap < slot)
+            score += double(slot - gap) * weight[dy * dy + dz * dz] * along[std::abs(cx) / 4];
+        }
+      }
+    if (score < best) {
+      best = score;
+      mul = m;
+    }
+  }
+  return mul;
+}
+
+// The multipliers of an n^3 grid for tables of FP32 and of FP64 sums.  The search
+// takes 12 us of a host core, a pass of the no-allocation call a few hundred, so
+// each grid size is searched once a process and kept: both are 24 bits, one word
+// a size, written whole (threads that race find the same), no heap and no
+// thread-local storage, whose first use in a thread allocates.
+struct LineMultipliers {
+  uint32_t fp32, fp64;
+};
+inline LineMultipliers line_multipliers(int n) {
+  static std::atomic<uint64_t> known[4097];  // by n; 0: not searched (multipliers are odd)
+  std::atomic<uint64_t>& of_n = known[n];
+  uint64_t v = of_n.load(std::memory_order_relaxed);
+  if (!v) {
+    v = uint64_t(line_multiplier(n, kLog2LinesFp32)) << 32 | line_multiplier(n, kLog2LinesFp64);
+    of_n.store(v, std::memory_order_relaxed);
+  }
+  return {uint32_t(v >> 32), uint32_t(v)};
+}
 
 // Launch parameters that the autotuner times, in order: the library's default,
 // the ones in use (`now`), and a grid around them.  The first two are there

@@ -1,7 +1,9 @@
 // Host check (test infrastructure) of the plans in csrc/plan.h, one check a
 // name on the command line.  Built and run by tests/test_plan.py.
+#include <chrono>
 #include <cstdio>
 #include <cstring>
+#include <thread>
 
 #include "plan.h"
 
@@ -78,12 +80,44 @@ static int tuning_candidates() {
   return 0;
 }
 
+// the kept multipliers are the search's for every grid size, whatever threads
+// ask first; and sizes that alternate are not searched again (the time of 2000
+// pairs of calls against that of 200 searches)
+static int line_multipliers() {
+  int wrong[4] = {0, 0, 0, 0};
+  std::thread th[4];
+  for (int t = 0; t < 4; ++t)
+    th[t] = std::thread([t, &wrong] {
+      for (int k = 0; k < 4096; ++k) {
+        const int n = t % 2 ? 4096 - k : 1 + k;
+        const nrt::LineMultipliers m = nrt::line_multipliers(n);
+        wrong[t] += m.fp32 != nrt::line_multiplier(n, nrt::kLog2LinesFp32) ||
+                    m.fp64 != nrt::line_multiplier(n, nrt::kLog2LinesFp64) || m.fp32 % 2 == 0 ||
+                    m.fp64 % 2 == 0 || m.fp32 >> 24 || m.fp64 >> 24;
+      }
+    });
+  for (auto& x : th) x.join();
+  CHECK(wrong[0] + wrong[1] + wrong[2] + wrong[3] == 0);
+  using Clock = std::chrono::steady_clock;
+  const auto t0 = Clock::now();
+  uint32_t sum = 0;
+  for (int k = 0; k < 2000; ++k)
+    sum += nrt::line_multipliers(24).fp32 + nrt::line_multipliers(40).fp64;
+  const auto t1 = Clock::now();
+  for (int k = 0; k < 200; ++k) sum += nrt::line_multiplier(24 + k % 7, 7);
+  const auto t2 = Clock::now();
+  CHECK(t1 - t0 < t2 - t1);
+  std::printf("%u\n", sum);  // uses the loops' results
+  return 0;
+}
+
 int main(int argc, char** argv) {
   for (int a = 1; a < argc; ++a) {
     int bad = 1;
     if (!std::strcmp(argv[a], "merge_bins")) bad = merge_bins();
     if (!std::strcmp(argv[a], "split_length")) bad = split_length();
     if (!std::strcmp(argv[a], "tuning_candidates")) bad = tuning_candidates();
+    if (!std::strcmp(argv[a], "line_multipliers")) bad = line_multipliers();
     if (bad) {
       std::printf("%s failed\n", argv[a]);
       return 1;

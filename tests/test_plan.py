@@ -20,7 +20,19 @@ def check(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("name", ["merge_bins", "split_length", "tuning_candidates"])
+@pytest.mark.parametrize("name", ["merge_bins", "split_length", "tuning_candidates",
+                                  "line_multipliers"])
 def test_plan(check, name):
     p = subprocess.run([check, name], capture_output=True, text=True, timeout=60)
     assert p.returncode == 0, p.stdout + p.stderr
+
+
+def test_thread_local_storage_holds_messages_only():
+    """The first use of a loaded library's thread-local storage in a thread
+    allocates it, so the no-allocation call may use none on its way to NRT_OK:
+    the one thread-local is the message of a failed call."""
+    import paper_2512_12466_amd as nrt
+    out = subprocess.run(["readelf", "-sW", nrt.LIB_PATH], check=True, capture_output=True,
+                         text=True).stdout
+    tls = [line.split()[-1] for line in out.splitlines() if " TLS " in line]
+    assert tls and all("g_init_error" in s for s in tls), tls
