@@ -5,8 +5,6 @@
 #include <cmath>
 #include <cstring>
 #include <new>
-#include <system_error>
-#include <thread>
 
 #include "healpix.h"
 #include "internal.h"
@@ -371,25 +369,6 @@ nrt_status trace_pass(nrt_ctx* c, double* gamma, nrt_budget* out) {
   return NRT_OK;
 }
 
-// fn(lo, hi) over [0, count) on up to 16 threads; on this one alone below
-// `least` items a thread, and for a thread that cannot be started
-template <typename Fn>
-void over_threads(int64_t count, int64_t least, Fn fn) {
-  const int64_t most = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-  const int64_t nt = std::max<int64_t>(1, std::min(most, count / least));
-  std::thread th[16];
-  for (int64_t t = 1; t < nt; ++t) {
-    try {
-      th[t] = std::thread(fn, count * t / nt, count * (t + 1) / nt);
-    } catch (const std::system_error&) {
-      fn(count * t / nt, count * (t + 1) / nt);
-    }
-  }
-  fn(int64_t(0), count / nt);
-  for (auto& x : th)
-    if (x.joinable()) x.join();
-}
-
 // The direction table of levels 0..c->lay.dir_levels.  Its cosines and sines
 // are the C library's, computed on the host; the pixels of all levels share
 // 4^top / 2 azimuths (one for 32 pixels), so the host evaluates those and the
@@ -406,7 +385,7 @@ nrt_status fill_direction_table(nrt_ctx* c) {
   std::vector<double> tab;
   try {
     tab.resize(size_t(azimuths) * 2);
-    over_threads(azimuths, 8192, [&](int64_t lo, int64_t hi) {
+    nrt::over_threads(azimuths, 8192, [&](int64_t lo, int64_t hi) {
       // ring of entry lo: the largest nr with (nr - 1)(nr - 2) / 2 <= lo
       int nr = int(1.5 + std::sqrt(2.0 * double(lo) + 0.25));
       while (nrt::hp_azimuth_index(nr, 1) > lo) --nr;

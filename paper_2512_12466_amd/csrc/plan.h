@@ -9,6 +9,8 @@
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
+#include <thread>
 #include <vector>
 
 #include "nyxrt.h"
@@ -121,6 +123,27 @@ inline double split_length(double n_min_ray, int level) {
   double s;
   std::memcpy(&s, &hi, sizeof(s));
   return s;
+}
+
+// fn(lo, hi) over [0, count) on up to 16 threads; on this one alone below
+// `least` items a thread, and for a thread that cannot be started, whether the
+// system has none left or there is no memory for it (either would leave running
+// threads behind an exception, which ends the process).  fn must not throw.
+template <typename Fn>
+void over_threads(int64_t count, int64_t least, Fn fn) {
+  const int64_t most = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+  const int64_t nt = std::max<int64_t>(1, std::min(most, count / least));
+  std::thread th[16];
+  for (int64_t t = 1; t < nt; ++t) {
+    try {
+      th[t] = std::thread(fn, count * t / nt, count * (t + 1) / nt);
+    } catch (const std::exception&) {
+      fn(count * t / nt, count * (t + 1) / nt);
+    }
+  }
+  fn(int64_t(0), count / nt);
+  for (auto& x : th)
+    if (x.joinable()) x.join();
 }
 
 // Bins per axis of the merge's overlap search in an n^3 box: none narrower than

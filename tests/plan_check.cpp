@@ -2,7 +2,9 @@
 // name on the command line.  Built and run by tests/test_plan.py.
 #include <chrono>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <new>
 #include <thread>
 
 #include "plan.h"
@@ -14,6 +16,35 @@
       return 1;                                               \
     }                                                         \
   } while (0)
+
+// allocations still allowed; negative: any number
+static std::atomic<int> g_allowed{-1};
+__attribute__((noinline)) void* operator new(size_t bytes) {
+  if (g_allowed >= 0 && g_allowed-- == 0) {
+    g_allowed = 0;
+    throw std::bad_alloc();
+  }
+  if (void* p = std::malloc(bytes)) return p;
+  throw std::bad_alloc();
+}
+__attribute__((noinline)) void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { operator delete(p); }
+
+// every item once, also when there is memory for the first threads only
+static int over_threads() {
+  for (int64_t count : {0, 1, 99, 100, 1000, 1001, 4096})
+    for (int allowed : {-1, 0, 1, 2, 5}) {
+      std::vector<std::atomic<int>> seen(4096);
+      std::atomic<int>* s = seen.data();
+      g_allowed = allowed;
+      nrt::over_threads(count, 100, [s](int64_t lo, int64_t hi) {
+        for (int64_t q = lo; q < hi; ++q) ++s[q];
+      });
+      g_allowed = -1;
+      for (int64_t q = 0; q < 4096; ++q) CHECK(seen[size_t(q)] == (q < count ? 1 : 0));
+    }
+  return 0;
+}
 
 // a bin's index and the mark of a source without a bin share 32 bits, and the
 // pair kernel's arithmetic is in int
@@ -118,6 +149,7 @@ int main(int argc, char** argv) {
     if (!std::strcmp(argv[a], "split_length")) bad = split_length();
     if (!std::strcmp(argv[a], "tuning_candidates")) bad = tuning_candidates();
     if (!std::strcmp(argv[a], "line_multipliers")) bad = line_multipliers();
+    if (!std::strcmp(argv[a], "over_threads")) bad = over_threads();
     if (bad) {
       std::printf("%s failed\n", argv[a]);
       return 1;

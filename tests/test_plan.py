@@ -21,7 +21,7 @@ def check(tmp_path_factory):
 
 
 @pytest.mark.parametrize("name", ["merge_bins", "split_length", "tuning_candidates",
-                                  "line_multipliers"])
+                                  "line_multipliers", "over_threads"])
 def test_plan(check, name):
     p = subprocess.run([check, name], capture_output=True, text=True, timeout=60)
     assert p.returncode == 0, p.stdout + p.stderr
