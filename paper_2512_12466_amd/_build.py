@@ -11,10 +11,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libnyxrt.so")
-# the same sources with the sizes at which the march changes its cell index and
-# table set low, so that tests reach both sides of them on small grids
+# the same sources with the sizes at which the march changes its cell index,
+# table and counts set low, so that tests reach both sides of them on small grids
 EDGE_LIB = os.path.join(HERE, "libnyxrt_edges.so")
-EDGE_FLAGS = ["-DNRT_NARROW_CELLS=0", "-DNRT_TABLE_LINES=1000"]
+EDGE_FLAGS = ["-DNRT_NARROW_CELLS=0", "-DNRT_TABLE_LINES=1000",
+              "-DNRT_SEGMENT_FOLD=50"]
 SOURCES = ["capi.hip", "trace.hip", "spectrum.hip", "chem.hip", "merge.hip", "noalloc.hip"]
 ARCH = os.environ.get("NYXRT_OFFLOAD_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

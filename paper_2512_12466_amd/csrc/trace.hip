@@ -92,7 +92,7 @@ __device__ __forceinline__ ArgsK& fresh_args() {
 
 struct LaneAcc {
   double absorbed = 0.0, escaped = 0.0, truncated = 0.0;
-  uint32_t segments = 0;  // of one lane in one launch
+  uint32_t segments = 0;  // of one lane, since they were last added up
 };
 
 // Per-wavefront Gamma accumulator in LDS.  A wavefront marches rays claimed
@@ -120,14 +120,18 @@ constexpr int kLine = 8;
 constexpr int kProbe = 16;
 constexpr uint32_t kEmpty = 0xffffffffu;
 
-// Sizes at which the march's cell index and table change.  A second build of
-// the library, for the tests, sets them so that small grids take the 64-bit
-// index and both sides of the table's limit.
+// Sizes at which the march's cell index, table and counts change.  A second
+// build of the library, for the tests, sets them so that small grids take the
+// 64-bit index, both sides of the table's limit and the early sums.
 #ifndef NRT_NARROW_CELLS
 #define NRT_NARROW_CELLS (int64_t(1) << 32)  // most cells of the 32-bit index
 #endif
 #ifndef NRT_TABLE_LINES
 #define NRT_TABLE_LINES int64_t(kEmpty)  // lines below this many have a key
+#endif
+
+#ifndef NRT_SEGMENT_FOLD
+#define NRT_SEGMENT_FOLD (uint32_t(1) << 31)  // a lane's segments that are added up early
 #endif
 
 template <typename V, typename Idx>
@@ -899,6 +903,12 @@ __attribute__((amdgpu_waves_per_eu((MIXED || PERIODIC || !POLY) ? 4 : 3, 8))) vo
       if (pool == pool_end && first_runs >= total) {
         exhausted = true;  // the first runs were all: no claim is needed to tell
       } else if (pool == pool_end) {
+        // a run is at most 65536 rays of 12300 cells, so that a lane's 32-bit
+        // count cannot pass 2^32 before the next claim
+        if (acc.segments >= NRT_SEGMENT_FOLD) {
+          atomicAdd(&F.acc->segments, static_cast<unsigned long long>(acc.segments));
+          acc.segments = 0;
+        }
         // what is left by this wavefront's last run (others may have taken more)
         const int64_t left = total - (pool > first_runs ? pool : first_runs);
         run = run_size(int64_t(iterations) * kCellsPerIteration * 64 / run, brief, left, share,

@@ -54,3 +54,26 @@ def test_wide_index(edges, orc, n, periodic, corr, spectrum):
         assert np.abs(got[mask] / ref[mask] - 1).max() <= tol, prec
         for k in ("absorbed", "escaped", "truncated"):
             assert abs(b[k] - rb[k]) <= (1e-10 if prec == 0 else 1e-6) * rb["emitted"], (prec, k)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_segment_counts_added_early(edges, orc, prec):
+    """A lane's 32-bit count of segments is added to the pass's 64-bit one before
+    it can wrap (2^31; 50 in the second build): the count is the oracle's, in
+    runs of 64 that make every wavefront claim often."""
+    n = 24
+    g = np.random.default_rng(17)
+    nH = 1e-3 * np.exp(g.standard_normal((n, n, n)))
+    x = np.full((n, n, n), 0.9)
+    pos, ndot = W.uniform_positions(12, n, g), W.lognormal_values(12, 1e50, 1.0, g)
+    h = 0.1 / (W.SIGMA0 * 1e-3)
+    kw = dict(periodic=True, n_min_ray=4.0, l_max=6, tau_max=30.0)
+    _, rb = orc.trace(orc.make_params(n, h, **kw), nH, x, pos, ndot)
+    ctx = edges.init_grid(edges.make_desc(n, h, precision=prec, **kw), nH, x, device="cuda:0",
+                          max_sources=12, ray_capacity=1 << 20)
+    ctx.add_sources(pos, ndot)
+    for refill, bpc in ((0, 0), (1, 1), (64, 1)):
+        ctx.set_tuning(refill_min=refill, claim=64 if bpc else 0, blocks_per_cu=bpc)
+        _, b = ctx.trace_step()
+        assert b["segments"] == rb["segments"] > 50 * rb["rays"] / 64
+    ctx.destroy()
