@@ -57,25 +57,27 @@ WORKLOADS = {  # name -> generator in workloads/ (configs 1-5 of the method's te
 # host-driven in chunks of a quarter of a queue, and each chunk launch ends
 # in a tail of long rays, so fewer, larger chunks pay (2^27: 32 GB of queues)
 DEFAULT_CAPACITY = {"late-reion-1024-262144src": 1 << 29}
-# launch parameters (refill_min, claim) frozen for these workloads; the others
-# keep the library's defaults.  The 128^3 and 512^3 ones date from a march that
-# refilled at 16 idle lanes; --launch 0,0 (the library's own) is faster there
-# now: 128^3 11.88 -> 9.99 ms, 512^3 FP64 7.64 -> 7.23.  --tune picks again,
-# --launch overrides.
+# launch parameters (refill_min, claim) that nrt_autotune picked for these
+# workloads.  A run without --launch takes them only where they are still the
+# faster (IN_USE); the others date from a march that refilled at 16 idle lanes.
 TUNED = {"lognormal-128-64src": (16, 64), "clustered-512-32768src": (16, 256),
-         # long rays in bubbles: a run is taken and retired whole (refill only
-         # a drained wavefront; a pass takes 7857 ms, 7930 with the library's)
-         "late-reion-1024-262144src": (64, 64),
-         # a polychromatic pass keeps whole sibling runs alive: refill only a
-         # drained wavefront
-         "lognormal-128-64src+spectrum": (64, 64)}
+         "late-reion-1024-262144src": (64, 64), "lognormal-128-64src+spectrum": (64, 64)}
+# ms a pass, frozen / the library's own: late-reion-1024 mixed 7817 / 7888;
+# lognormal-128 mixed 11.81 / 9.90, FP64 13.46 / 12.08; clustered-512 6.88 / 6.84,
+# 7.63 / 7.18; blackbody 302.7 / 302.9, 387.4 / 387.4
+IN_USE = {"late-reion-1024-262144src"}
 
 
 def launch_params(workload, spectrum_kind=0):
-    """The frozen (refill_min, claim) of a workload, or None for the library's defaults."""
+    """The frozen (refill_min, claim) of a workload, or None if it has none."""
     if spectrum_kind and workload + "+spectrum" in TUNED:
         return TUNED[workload + "+spectrum"]
     return TUNED.get(workload)
+
+
+def run_launch(workload, spectrum_kind=0):
+    """The (refill_min, claim) of a run without --launch, or None for the library's own."""
+    return launch_params(workload, spectrum_kind) if workload in IN_USE else None
 
 
 def make_workload(name):
@@ -564,7 +566,7 @@ def main():
                     help="source spectrum: mono (13.6 eV), bb:<T> (blackbody at T kelvin) or "
                          "pl:<alpha> (power law)")
     ap.add_argument("--launch", default="",
-                    help="refill_min,claim launch parameters (overrides the workload's frozen ones)")
+                    help="refill_min,claim launch parameters (0,0: the library's own)")
     ap.add_argument("--tune", action="store_true",
                     help="pick launch parameters with nrt_autotune before timing")
     ap.add_argument("--calibrate-copy", type=int, default=0, metavar="MIB",
@@ -596,7 +598,7 @@ def main():
         log(f"device copy: {copy_gbs:.0f} GB/s (read + write)")
     spectrum = parse_spectrum(args.spectrum)
     launch = (tuple(int(v) for v in args.launch.split(",")) if args.launch
-              else launch_params(args.workload, spectrum[0]))
+              else run_launch(args.workload, spectrum[0]))
     if not args.capacity:
         args.capacity = DEFAULT_CAPACITY.get(args.workload, 1 << 25)
     w = make_workload(args.workload)

@@ -116,3 +116,11 @@ def test_more_than_one_gpu_exits():
     p = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"],
                        capture_output=True, text=True, timeout=120)
     assert p.returncode == 2 and "one GPU" in p.stderr
+
+
+def test_a_run_takes_frozen_parameters_only_where_they_are_the_faster():
+    assert bench.run_launch("late-reion-1024-262144src") == (64, 64)
+    for w in ("lognormal-128-64src", "clustered-512-32768src", "lognormal-256-4096src-bubbles",
+              "stromgren-testA-32"):
+        assert bench.run_launch(w) is None
+    assert bench.run_launch("lognormal-128-64src", 1) is None
