@@ -4,15 +4,16 @@
 //      same-cell sources by summing rates in input order;
 //   2. max_radius: one wavefront per source grows shells r = k dr <= R_max;
 //      the shell's samples are the distinct cells floor(centre + r d_q) over
-//      the HEALPix directions d_q of `shell_level` (deduplicated with a hash
-//      set in LDS); a shell passes iff N_ion / N_tot >= f_req, or, below
-//      N_min samples, iff every sample is ionized;
+//      the HEALPix directions d_q of `shell_level` (told apart in LDS, by a
+//      bitmap of the cube around the source for radii to 14.5 cells in boxes of
+//      31 and more, else by a hash set); a shell passes iff N_ion / N_tot >=
+//      f_req, or, below N_min samples, iff every sample is ionized;
 //   3. pairs with min-image d^2 <= (f_ov (r_a + r_b))^2 + eps and r_a, r_b > 0
 //      are united in a lock-free union-find (the larger root is hooked under
 //      the smaller, so a group's root is its lowest member); candidates come
 //      from a uniform binning whose bins are wider than any overlap distance;
 //   4. (root, index) pairs are sorted so each group's members are contiguous
-//      and in order; one thread per group sums rates, takes the largest
+//      and in order; one wavefront per group sums rates, takes the largest
 //      radius, forms the flux-weighted centroid with periodic unwrapping
 //      relative to the lowest member, rounds it (floor(c + 1/2)), wraps it and
 //      snaps it to the nearest member cell (ties: lowest member);

@@ -1221,13 +1221,16 @@ namespace {
 
 // The march instantiation for a precision, correction mode, boundary and
 // spectrum, and:
-//  - the sums of the deposit table.  FP64, except in the mixed path's first
-//    levels: LDS adds FP32 lane by lane (3.1 cycles each), so FP64 sums are
-//    faster as well as more exact (128^3 mixed, levels 5 and up: see
-//    LineTable), but the cells next to a source, which take their few
-//    deposits from rays of levels 0..4 (within 4 cells), keep the FP32 sums
-//    that set their values; those levels are a small part of any pass whose
-//    rays reach further;
+//  - the sums of the deposit table: FP64, except in the mixed path's levels 0..4.
+//    These set the values around a source (a level-4 ray ends 7.8 cells from it
+//    at N_min = 4), and all of them where rays go no deeper (n_min_ray = 0,
+//    l_max < 5).  FP64 sums there would be a little faster and a little more
+//    exact, but move Gamma by 2e-8 to 3e-8 of itself (its error against 64 bits:
+//    6.5e-8 FP32, 4.7e-8 FP64 at 128^3, 7.7e-8 and 7.5e-8 at 256^3), and a path
+//    keeps the values that it gave.  What FP32 costs, against FP64 everywhere: an
+//    LDS add takes the lanes one by one (3.1 cycles each); open 97^3 676 / 617 us,
+//    128^3 10.25 / 10.10 ms, 256^3 12.5 / 11.8, 512^3 7.21 / 6.88, unsplit rays of
+//    330 cells 2.79 / 2.43; rays of 5 cells 1.06 / 1.19;
 //  - the cell index: 32 bits while n^3 <= 2^32 (n <= 1625), else 64.
 using MarchKernel = void (*)(MarchArgs);
 constexpr int kFirstWideSumLevel = 5;
@@ -1285,8 +1288,8 @@ hipError_t launch_march_on(const nrt_grid_desc& d, int cu_count, int resident_pe
   // children are queued side by side, so the next level's runs are bundles
   // again).  Measured, refill at 16 / 64: 1024^3 mixed 351 / 221 ms, 128^3
   // mixed 12.6 / 10.8, FP64 15.7 / 14.2, blackbody 35.7 / 26.8, 256^3 11.5 /
-  // 10.4.  Launches with FP32 sums keep the 16 lanes and 128 rays that their
-  // sums' order follows.
+  // 10.4.  Launches with FP32 sums keep the 16 lanes and 128 rays, which set the
+  // order of their sums and so their rounding.
   const bool wide = wide_sums(d, a.level);
   a.refill_min = t.refill_min > 0 ? t.refill_min : (wide ? 64 : 16);
   a.claim = t.claim > 0 ? t.claim : (wide ? 256 : 128);

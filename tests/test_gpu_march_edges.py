@@ -147,3 +147,31 @@ def test_first_runs(gpu, m, prec):
         for k in ("absorbed", "escaped", "truncated"):
             assert abs(b[k] - ref[k]) <= (1e-10 if prec == 0 else 1e-6) * ref["emitted"], k
     ctx.destroy()
+
+
+@pytest.mark.parametrize("periodic", [True, False])
+@pytest.mark.parametrize("kw", [dict(n_min_ray=0.0, l_max=7), dict(n_min_ray=0.05, l_max=4)])
+def test_mixed_sums_of_the_first_levels(gpu, orc, periodic, kw):
+    """Mixed passes whose long rays never reach the levels that are summed in
+    FP64: every deposit is summed in FP32 slots, within the method's 1e-4."""
+    n = 48
+    g = np.random.default_rng(21 + periodic)
+    nH = 1e-3 * np.exp(g.standard_normal((n, n, n)))
+    x = np.where(g.random((n, n, n)) < 0.5, 1.0 - 1e-4, 0.9)
+    pos, ndot = W.uniform_positions(200, n, g), W.lognormal_values(200, 1e50, 1.0, g)
+    h = 0.2 / (W.SIGMA0 * 1e-3)
+    kw = dict(periodic=periodic, tau_max=30.0, n_th=4e-4, **kw)
+    ref, rb = orc.trace(orc.make_params(n, h, **kw), nH, x, pos, ndot)
+    assert rb["segments"] > 10 * rb["rays"] and sum(rb["rays_per_level"][5:]) == 0
+    ctx = gpu.init_grid(gpu.make_desc(n, h, precision=1, **kw), nH, x, device="cuda:0",
+                        max_sources=200, ray_capacity=1 << 20)
+    ctx.add_sources(pos, ndot)
+    gamma, b = ctx.trace_step()
+    got = gamma.cpu().numpy()
+    ctx.destroy()
+    for k in ("segments", "rays", "splits"):
+        assert b[k] == rb[k], k
+    mask = ref > 1e-6 * ref.max()
+    assert np.abs(got[mask] / ref[mask] - 1).max() <= 1e-4
+    for k in ("absorbed", "escaped", "truncated"):
+        assert abs(b[k] - rb[k]) <= 1e-6 * rb["emitted"], k
