@@ -900,8 +900,11 @@ __attribute__((amdgpu_waves_per_eu((MIXED || PERIODIC || !POLY) ? 4 : 3, 8))) vo
     const int n_idle = __popcll(idle);
     if (!exhausted && (n_idle >= A.refill_min || n_idle == 64)) {
       ArgsK& F = fresh_args();
-      if (pool == pool_end && first_runs >= total) {
-        exhausted = true;  // the first runs were all: no claim is needed to tell
+      // The first runs were all: no claim is needed to tell.  (FP32 sums: the wait
+      // for one is part of the timing that orders the children they are queued
+      // with, and so of the sums' rounding, which otherwise moves by 3e-9.)
+      if (sizeof(V) == 8 && pool == pool_end && first_runs >= total) {
+        exhausted = true;
       } else if (pool == pool_end) {
         // a run is at most 65536 rays of 12300 cells, so that a lane's 32-bit
         // count cannot pass 2^32 before the next claim
