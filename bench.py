@@ -338,7 +338,7 @@ def roofline(path, res, counters=None, copy_gbs=None):
 
 
 KERNEL_SOURCES = ["paper_2512_12466_amd/csrc/trace.hip", "paper_2512_12466_amd/csrc/healpix.h",
-                  "paper_2512_12466_amd/csrc/internal.h"]
+                  "paper_2512_12466_amd/csrc/internal.h", "paper_2512_12466_amd/csrc/plan.h"]
 
 
 def counters_file(workload):

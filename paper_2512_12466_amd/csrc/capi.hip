@@ -376,7 +376,7 @@ nrt_status trace_pass(nrt_ctx* c, double* gamma, nrt_budget* out) {
 // levels 0..9: 2 ms, where the host took 30 for the vectors and their copy).
 // Azimuths that do not fit the scratch space (levels past 9 on grids below
 // 128^3) go through it in windows, each launch writing the vectors of its
-// window (levels 0..10 at 32^3: 2.0 ms, 0..11 at 64^3: 8.7 ms; vectors formed on
+// window (levels 0..10 at 32^3: 1.1 ms, 0..11 at 64^3: 4.7 ms; vectors formed on
 // the host took 112 and 418).
 nrt_status fill_direction_table(nrt_ctx* c) {
   const int top = c->lay.dir_levels;
